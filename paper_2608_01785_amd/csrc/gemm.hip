@@ -39,6 +39,7 @@
 // and in alternating block order from round to round.
 #include <type_traits>
 
+#include "gemm_policy.h"
 #include "hs_device.h"
 #include "hs_kernels.h"
 
@@ -524,9 +525,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs a) {
                 if (a.rope) {
 #pragma unroll
                   for (int e = 0; e < 4; ++e) {
-                    const float2 cs = rt[d + e];
-                    rl[h][e] = lo[e] * cs.x - hi[e] * cs.y;
-                    rh[h][e] = hi[e] * cs.x + lo[e] * cs.y;
+                    rope_rotate(lo[e], hi[e], rt[d + e], rl[h][e], rh[h][e]);
                   }
                 } else {
 #pragma unroll
@@ -583,6 +582,8 @@ hipError_t launch_gemm(int epi, const GemmArgs& a, int max_blocks, hipStream_t s
   if (a.M <= 0) return hipSuccess;
   if (a.K < BK * kUnroll || a.K % (BK * kUnroll) != 0) return hipErrorInvalidValue;
   if (a.sumsq_out || a.scaled_out || a.row_sumsq) return hipErrorInvalidValue;
+  const int tile = gemm_tile_choice(a.M, a.n_tiles_n * 256, a.K, max_blocks);
+  if (tile >= 0) return launch_gemm_tile(epi, a, tile, s);
   switch (epi) {
     case EPI_RESID: return launch_one<EPI_RESID, 128>(a, max_blocks, s);
     case EPI_SWIGLU: return launch_one<EPI_SWIGLU, 128>(a, max_blocks, s);

@@ -247,6 +247,13 @@ __device__ __forceinline__ int rope_pos(const Args& a, int m, int j) {
   return a.pos[c * a.pos_stride + m];
 }
 
+// One rotation pair: (lo, hi) -> (lo cos - hi sin, hi cos + lo sin), with the
+// roundings spelled out so that every GEMM gives the same bits.
+__device__ __forceinline__ void rope_rotate(float lo, float hi, float2 cs, float& rl, float& rh) {
+  rl = fmaf(lo, cs.x, -(hi * cs.y));
+  rh = fmaf(hi, cs.x, lo * cs.y);
+}
+
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
