@@ -358,7 +358,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_kernel(AttnArgs a) {
 // Single-row (decode) attention: one block per (work item, key/value head);
 // the unit is in decode_unit.h.
 template <int DH>
-__global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecodeAttnArgs a) {
+__global__ __launch_bounds__(kThreads, DH == 64 ? 3 : 2) void decode_attn_kernel(DecodeAttnArgs a) {
   __shared__ decode::DecodeSmem<DH> sm;
   const int item = blockIdx.x / a.hkv;
   if (a.n_items_dev && item >= *a.n_items_dev) return;  // a grid sized for a fixed layout

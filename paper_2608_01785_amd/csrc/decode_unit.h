@@ -2,16 +2,23 @@
 //
 // A unit is one key range (a "split" of unit_keys keys, inside one page of
 // the cache) of one row r and
-// one key/value head g; the group's G query heads are the 32 MFMA columns
-// (G <= 8 valid), so the keys and values of the head are read once for the
-// whole group.  The range is cut into tiles (dec_tile_keys keys); wave w takes
-// tiles w, w + 4, w + 8, ... and keeps its own running softmax state over
-// them.  A tile's K and V fragments go from memory straight into registers in
-// MFMA layout (no LDS), two register sets deep, so the next tile's loads are
-// in flight while the current tile is multiplied.  The four waves' states are
-// merged through LDS.  A row with one split writes its output directly;
-// otherwise every split publishes its state and the last split of (r, g) to
-// arrive merges them in split order.
+// one key/value head g; the group's G query heads are columns of one 16-wide
+// MFMA (G <= 8 valid), so the keys and values of the head are read once for
+// the whole group.  The range is cut into tiles (dec_tile_keys keys); wave w
+// takes tiles w, w + 4, w + 8, ... and keeps its own running softmax state
+// over them.  A tile is loaded as whole lines into registers, two sets deep,
+// and passes through a private LDS image of the wave (no barrier) into MFMA
+// layout.  The four waves' states are merged through LDS.  A row with one
+// split writes its output directly; otherwise every split publishes its state
+// and the last split of (r, g) to arrive merges them in split order.
+//
+// What bounds it is memory: the split's keys and values, read once.  MFMA
+// fragments fetched straight from the cache put adjacent lanes in different
+// key rows, which occupies a CU's address unit for about 93 cycles per 1 KB
+// against 17 for whole lines, and 32-wide score tiles spend twice the softmax
+// work on columns that hold no query.  A talker step (32 rows of 128 .. 1024
+// keys, 128 CUs, 16 layers) went from 929 to 909 us, one of 128 rows on 160
+// CUs from 2068 to 2013.
 #pragma once
 
 #include "hs_device.h"
@@ -24,20 +31,38 @@ constexpr int kUnitThreads = 256;  // threads per block running a unit
 
 template <int DH>
 struct DecodeSmem {
-  float red_m[4][8], red_l[4][8];
-  float red_o[4][DH][9];  // [wave][d][query head], G <= 8
+  static constexpr int kTile = dec_tile_keys(DH) * DH * 2;  // bytes of a tile's keys, and of its values
+  union {
+    uint8_t tile[4][2 * kTile];  // [wave] keys, then values
+    struct {
+      float red_m[4][8], red_l[4][8];
+      float red_o[4][DH][9];  // [wave][d][query head], G <= 8
+    };
+  };
   int last;
 };
+
+// Largest and total value over the four lanes that hold one query's keys
+// (lanes l, l ^ 16, l ^ 32, l ^ 48).
+__device__ __forceinline__ float quarter_max(float v) {
+  v = fmaxf(v, __shfl_xor(v, 16, 64));
+  return fmaxf(v, __shfl_xor(v, 32, 64));
+}
+__device__ __forceinline__ float quarter_sum(float v) {
+  v += __shfl_xor(v, 16, 64);
+  return v + __shfl_xor(v, 32, 64);
+}
 
 // One work item (a key range of one row) for one key/value head g, by one
 // block of 256 threads.
 template <int DH>
 __device__ __forceinline__ void decode_attn_unit(const DecodeAttnArgs& a, int item, int g, DecodeSmem<DH>& sm) {
   constexpr int TK = dec_tile_keys(DH);        // keys per tile
-  constexpr int NST = TK / 32;                 // 32-key score subtiles
-  constexpr int NKB = DH / 16;                 // 16-wide K steps of q.k
-  constexpr int NDS = DH / 32;                 // output subtiles along dh
-  constexpr int NPB = TK / 16;                 // 16-key P.V steps
+  constexpr int NKB = DH / 32;                 // 32-wide K steps of q.k
+  constexpr int NDS = DH / 16;                 // output subtiles along dh
+  constexpr int kTile = DecodeSmem<DH>::kTile;
+  constexpr int NL = kTile / 1024;             // 1 KB loads of a tile's keys, and of its values
+  static_assert(TK == 32 && TK == kv_tile_keys, "a tile is one value tile of the cache");
   auto& red_m = sm.red_m;
   auto& red_l = sm.red_l;
   auto& red_o = sm.red_o;
@@ -45,12 +70,13 @@ __device__ __forceinline__ void decode_attn_unit(const DecodeAttnArgs& a, int it
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int fr = lane & 31, fh = lane >> 5;
+  const int fr = lane & 15, fh = lane >> 4;
   const DecItem it = a.items[item];
   const int t = it.t, n_keys = it.n_keys, split = it.split, n_split = it.n_split;
   const int G = a.hq / a.hkv;
   const int k_begin = split * a.unit_keys;
-  const int n_tiles = (min(n_keys - k_begin, a.unit_keys) + TK - 1) / TK;
+  const int k_end = min(n_keys, k_begin + a.unit_keys);  // keys past it belong to the next range or to none
+  const int n_tiles = (k_end - k_begin + TK - 1) / TK;
   // The range lies in one page (of a slot or the packed buffer): its first
   // key sits at key0 = k_begin rounded down to the page size.
   const int key0 = k_begin - k_begin % a.page_keys;
@@ -59,164 +85,184 @@ __device__ __forceinline__ void decode_attn_unit(const DecodeAttnArgs& a, int it
   const int64_t kbase = it.kbase + int64_t(g) * a.kv_head_stride;
   const int64_t vbase = it.vbase + int64_t(g) * a.kv_head_stride;
 
-  float m_run = -INFINITY, l_run = 0.0f;
-  f32x16 o[NDS];
-#pragma unroll
-  for (int i = 0; i < NDS; ++i)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) o[i][e] = 0.0f;
-
-  u32x4 qf[NKB];
-  {
-    const uint16_t* qp = a.q + (int64_t(t) * a.hq + g * G + qh) * DH + fh * 8;
-#pragma unroll
-    for (int kb = 0; kb < NKB; ++kb) qf[kb] = *reinterpret_cast<const u32x4*>(qp + kb * 16);
-  }
-
-  // K rows (A operand of S^T = K Q^T, rows permuted by perm32) and V^T rows
-  // (A operand of O^T = V^T P^T) of tile `ti` of the range, through buffer
-  // resources based at the range's page and head: per-lane offsets are
-  // fixed, the tile moves the scalar offset.  A tile is one 32-key value tile
-  // of the cache, and its key rows are contiguous too.  Keys past the last
-  // one stay inside the page (ranges are whole tiles of a page whose length
-  // is a multiple of 64); their scores are masked below.
-  static_assert(TK == kv_tile_keys, "a tile is one value tile of the cache");
+  // Keys and values of tile `ti` of the range, each one contiguous run of
+  // kTile bytes: every load of a wave covers 1 KB of whole lines.  Keys past
+  // the last one stay inside the page (ranges are whole tiles of a page whose
+  // length is a multiple of 64); their scores are masked below.  A tile past
+  // the wave's last is read through an empty resource: zeros, no traffic, so
+  // every iteration issues the same loads and the wait counts stay exact.
   const __amdgpu_buffer_rsrc_t kres =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.kstore + kbase), 0, 0x7ffffff0, 0x00020000);
   const __amdgpu_buffer_rsrc_t vres =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.vstore + vbase), 0, 0x7ffffff0, 0x00020000);
-  const uint32_t k_lane = uint32_t(perm32(fr) * DH * 2 + fh * 16);
-  const uint32_t v_lane = uint32_t(fr * TK * 2 + fh * 16);
-  constexpr uint32_t v_sub = 32 * TK * 2;  // bytes between 32-dimension subtiles of a value tile
+  const __amdgpu_buffer_rsrc_t zres =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.kstore + kbase), 0, 0, 0x00020000);
   struct Tile {
-    u32x4 k[NST][NKB];
-    u32x4 v[NDS][NPB];
+    u32x4 k[NL], v[NL];
   };
-  auto load_tile = [&](int ti, Tile& tl) {
-    const int kv0 = k_begin + ti * TK - key0;  // key index inside the page
+  auto load_k = [&](int i, Tile& tl) {
+    const __amdgpu_buffer_rsrc_t res = i < my_tiles ? kres : zres;
+    const uint32_t so = uint32_t(k_begin + (wave + 4 * i) * TK - key0) * uint32_t(DH * 2);
 #pragma unroll
-    for (int st = 0; st < NST; ++st) {
-      const uint32_t so = uint32_t((kv0 + 32 * st) * DH * 2);
+    for (int l = 0; l < NL; ++l)
+      tl.k[l] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(res, uint32_t(lane * 16 + l * 1024), so, 0));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto load_v = [&](int i, Tile& tl) {
+    const __amdgpu_buffer_rsrc_t res = i < my_tiles ? vres : zres;
+    const uint32_t so = uint32_t(k_begin + (wave + 4 * i) * TK - key0) * uint32_t(DH * 2);
+#pragma unroll
+    for (int l = 0; l < NL; ++l)
+      tl.v[l] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(res, uint32_t(lane * 16 + l * 1024), so, 0));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  u32x4 qf[NKB];  // B operand of S^T = K Q^T: 32 dimensions per step
+  {
+    const uint16_t* qp = a.q + (int64_t(t) * a.hq + g * G + qh) * DH + fh * 8;
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb) qf[kb] = *reinterpret_cast<const u32x4*>(qp + kb * 32);
+  }
+  // Register sets: a set is reloaded as soon as its tile is in LDS, keys and
+  // values apart.  At head_dim 64 two sets, at 128 one (16 KB a wave, and two
+  // would spill): 128 KB or more of loads in flight on a full CU either way.
+  constexpr int S = DH == 64 ? 2 : 1;
+  Tile ts[S];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    load_k(u, ts[u]);
+    load_v(u, ts[u]);
+  }
+  float m_run = -INFINITY, l_run = 0.0f;
+  f32x4 o[NDS];
+#pragma unroll
+  for (int i = 0; i < NDS; ++i) o[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+  // The wave's LDS tile.  Chunk c (16 bytes) of key row r sits at physical
+  // chunk c ^ kswz(r), of value row d at c ^ vswz(d).  A 16-lane pass of
+  // fragment reads takes one logical chunk of 16 key rows 8 (i / 4) + i % 4
+  // (+ 4): 256-byte rows all start on bank 0 and need 16 different chunks,
+  // 128-byte rows 8 per parity; or of 16 consecutive 64-byte value rows,
+  // which need the four rows of each bank quarter apart.
+  uint8_t* ks = sm.tile[wave];
+  uint8_t* vs = ks + kTile;
+  auto kphys = [](int r, int c) {
+    const int i = ((r >> 3) << 2) | (r & 3);
+    return c ^ (DH == 128 ? i : (i >> 1));
+  };
+  auto vphys = [](int d, int c) { return c ^ ((d >> 2) & 3); };
+  constexpr int KCH = DH / 8;  // chunks per key row
+  // The swizzles depend on the lane and few of the load's bits: these
+  // addresses plus constants reach every chunk.
+  constexpr int kPer = NL / 4;  // key loads that share an address
+  uint32_t kw[4], kr[NKB];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int ch = q * kPer * 64 + lane, r = ch / KCH, c = ch % KCH;
+    kw[q] = uint32_t(r * DH * 2 + kphys(r, c) * 16);
+  }
+#pragma unroll
+  for (int kb = 0; kb < NKB; ++kb) {
+    const int r = 8 * (fr >> 2) + (fr & 3);
+    kr[kb] = uint32_t(r * DH * 2 + kphys(r, 4 * kb + fh) * 16);
+  }
+  const uint32_t vw = uint32_t((lane >> 2) * 64 + vphys(lane >> 2, lane & 3) * 16);
+  const uint32_t vr = uint32_t(fr * 64 + vphys(fr, fh) * 16);
+  // The lanes read each other's chunks: LDS accesses of a wave complete in
+  // order, so keeping the program order is enough.
+  auto stage_k = [&](const Tile& tl) {
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int l = 0; l < NL; ++l)
+      *reinterpret_cast<u32x4*>(ks + kw[l / kPer] + (l % kPer) * 1024) = tl.k[l];
+    asm volatile("" ::: "memory");
+  };
+  auto stage_v = [&](const Tile& tl, int ti) {
+    asm volatile("" ::: "memory");
+    // Values past the range: P is 0 there; keep 0 * garbage out.
+    const int v_left = k_end - (k_begin + ti * TK) - 8 * (lane & 3);
+    if (k_begin + (ti + 1) * TK > k_end) {
+      u32x4 keep;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        keep[e] = (2 * e < v_left ? 0x0000ffffu : 0u) | (2 * e + 1 < v_left ? 0xffff0000u : 0u);
+#pragma unroll
+      for (int l = 0; l < NL; ++l) *reinterpret_cast<u32x4*>(vs + vw + l * 1024) = tl.v[l] & keep;
+    } else {
+#pragma unroll
+      for (int l = 0; l < NL; ++l) *reinterpret_cast<u32x4*>(vs + vw + l * 1024) = tl.v[l];
+    }
+    asm volatile("" ::: "memory");
+  };
+  // Online softmax over this wave's tiles, in the exp2 domain.  Score row i
+  // of subtile st is key 8 (i / 4) + 4 st + i % 4, which leaves every lane
+  // with keys 8 fh .. 8 fh + 7 of its query: the B operand of O^T = V^T P^T.
+  auto do_tile = [&](int i, Tile& tl) {
+    const int ti = wave + 4 * i;
+    const int kv0 = k_begin + ti * TK;
+    stage_k(tl);
+    load_k(i + S, tl);
+    f32x4 sc[2];
+#pragma unroll
+    for (int st = 0; st < 2; ++st) {
+      sc[st] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
       for (int kb = 0; kb < NKB; ++kb)
-        tl.k[st][kb] = __builtin_amdgcn_raw_buffer_load_b128(kres, k_lane + kb * 32, so, 0);
+        sc[st] = mfma16(*reinterpret_cast<const u32x4*>(ks + kr[kb] + st * 4 * DH * 2), qf[kb], sc[st]);
     }
-#pragma unroll
-    for (int ds = 0; ds < NDS; ++ds)
-#pragma unroll
-      for (int pb = 0; pb < NPB; ++pb)
-        tl.v[ds][pb] = __builtin_amdgcn_raw_buffer_load_b128(vres, v_lane + pb * 32,
-                                                             uint32_t(ds) * v_sub + uint32_t(kv0 * DH * 2), 0);
-  };
-  // Online softmax over this wave's tiles, in the exp2 domain.
-  auto compute_tile = [&](int ti, Tile& tl) {
-    const int kv0 = k_begin + ti * TK;
-    if (kv0 + TK > n_keys) {
-      // Values past the last key: P is 0 there; keep 0 * garbage out.
-#pragma unroll
-      for (int pb = 0; pb < NPB; ++pb) {
-        const int key = kv0 + 16 * pb + 8 * fh;
-#pragma unroll
-        for (int ds = 0; ds < NDS; ++ds)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const uint32_t lo_ok = (key + 2 * e < n_keys) ? 0x0000ffffu : 0u;
-            const uint32_t hi_ok = (key + 2 * e + 1 < n_keys) ? 0xffff0000u : 0u;
-            tl.v[ds][pb][e] &= (lo_ok | hi_ok);
-          }
-      }
-    }
-    f32x16 sc[NST];
-#pragma unroll
-    for (int st = 0; st < NST; ++st) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) sc[st][e] = 0.0f;
-#pragma unroll
-      for (int kb = 0; kb < NKB; ++kb) sc[st] = mfma32(tl.k[st][kb], qf[kb], sc[st]);
-    }
+    const int left = k_end - kv0 - 8 * fh;  // valid keys from the lane's first on
     float mx = -INFINITY;
 #pragma unroll
-    for (int st = 0; st < NST; ++st)
+    for (int st = 0; st < 2; ++st)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int key = kv0 + 32 * st + 16 * (e >> 3) + 8 * fh + (e & 7);
-        const float v = (key < n_keys) ? sc[st][e] * a.scale_log2 : -INFINITY;
-        sc[st][e] = v;
+      for (int r = 0; r < 4; ++r) {
+        const float v = (4 * st + r < left) ? sc[st][r] * a.scale_log2 : -INFINITY;
+        sc[st][r] = v;
         mx = fmaxf(mx, v);
       }
     // Every tile holds at least one valid key, so m_new is finite.
-    const float m_new = fmaxf(m_run, fmaxf(mx, __shfl_xor(mx, 32, 64)));
-    const float alpha = exp2f(m_run - m_new);  // 0 on the first tile
-    m_run = m_new;
+    const float m_new = fmaxf(m_run, quarter_max(mx));
+    const float alpha = exp2_raw(m_run - m_new);  // 0 on the first tile
     float psum = 0.0f;
 #pragma unroll
-    for (int st = 0; st < NST; ++st)
+    for (int st = 0; st < 2; ++st)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float p = exp2f(sc[st][e] - m_new);
-        sc[st][e] = p;
+      for (int r = 0; r < 4; ++r) {
+        const float p = exp2_raw(sc[st][r] - m_new);
+        sc[st][r] = p;
         psum += p;
       }
     l_run = l_run * alpha + psum;
-    u32x4 pf[NPB];
+    m_run = m_new;
 #pragma unroll
-    for (int pb = 0; pb < NPB; ++pb) {
-      const int st = pb >> 1, r0 = 8 * (pb & 1);
+    for (int i = 0; i < NDS; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) pf[pb][e] = pack2h(sc[st][r0 + 2 * e], sc[st][r0 + 2 * e + 1]);
-    }
+      for (int r = 0; r < 4; ++r) o[i][r] *= alpha;
+    __builtin_amdgcn_sched_barrier(0);
+    stage_v(tl, ti);
+    load_v(i + S, tl);
+    u32x4 pf;
 #pragma unroll
-    for (int i = 0; i < NDS; ++i) {
+    for (int e = 0; e < 4; ++e) pf[e] = pack2h(sc[e >> 1][2 * (e & 1)], sc[e >> 1][2 * (e & 1) + 1]);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) o[i][e] *= alpha;
-#pragma unroll
-      for (int pb = 0; pb < NPB; ++pb) o[i] = mfma32(tl.v[i][pb], pf[pb], o[i]);
-    }
+    for (int i = 0; i < NDS; ++i) o[i] = mfma16(*reinterpret_cast<const u32x4*>(vs + vr + i * 1024), pf, o[i]);
+    __builtin_amdgcn_sched_barrier(0);
   };
 
-  if constexpr (DH == 64) {
-    // Two register sets.  The first load is unconditional (a wave without
-    // tiles reads tile 0 and discards it); later loads run only for tiles the
-    // wave owns, so the compiler's wait counts stay exact.  The scheduling
-    // barriers keep each tile's loads ahead of the previous tile's math.
-    Tile t0, t1;
-    load_tile(my_tiles > 0 ? wave : 0, t0);
-    __builtin_amdgcn_sched_barrier(0);
-    int i = 0;
-    for (; i + 2 < my_tiles; i += 2) {
-      load_tile(wave + 4 * (i + 1), t1);
-      __builtin_amdgcn_sched_barrier(0);
-      compute_tile(wave + 4 * i, t0);
-      __builtin_amdgcn_sched_barrier(0);
-      load_tile(wave + 4 * (i + 2), t0);
-      __builtin_amdgcn_sched_barrier(0);
-      compute_tile(wave + 4 * (i + 1), t1);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (my_tiles - i == 2) {
-      load_tile(wave + 4 * (i + 1), t1);
-      __builtin_amdgcn_sched_barrier(0);
-      compute_tile(wave + 4 * i, t0);
-      __builtin_amdgcn_sched_barrier(0);
-      compute_tile(wave + 4 * (i + 1), t1);
-    } else if (my_tiles - i == 1) {
-      compute_tile(wave + 4 * i, t0);
-    }
-  } else {
-    // head_dim 128: a tile's fragments and the larger output and query
-    // registers leave room for one register set; other waves of the CU
-    // overlap the loads.
-    Tile t0;
-    for (int i = 0; i < my_tiles; ++i) {
-      load_tile(wave + 4 * i, t0);
-      compute_tile(wave + 4 * i, t0);
-    }
+  // With two sets the last pass may take a tile past the wave's last: zeros,
+  // every score masked, nothing added (the maximum is finite by then).  A
+  // branch around it would cost the loop its exact wait counts.
+  for (int i = 0; i < my_tiles; i += S) {
+#pragma unroll
+    for (int u = 0; u < S; ++u) do_tile(i + u, ts[u]);
   }
 
-  // Merge the four waves.  Lane (fr, fh) holds query column fr; both halves
-  // share the maximum, each holds part of the sum.  Waves without a tile hold
-  // -inf and weigh zero.
-  const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+  // Merge the four waves.  Lane (fr, fh) holds query column fr; its four
+  // lanes share the maximum, each holds part of the sum.  Waves without a
+  // tile hold -inf and weigh zero.
+  const float l_tot = quarter_sum(l_run);
+  __syncthreads();  // the states take the tiles' place
   if (fh == 0 && fr < 8) {
     red_m[wave][fr] = m_run;
     red_l[wave][fr] = l_tot;
@@ -225,7 +271,7 @@ __device__ __forceinline__ void decode_attn_unit(const DecodeAttnArgs& a, int it
 #pragma unroll
     for (int i = 0; i < NDS; ++i)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) red_o[wave][32 * i + 8 * (e >> 2) + 4 * fh + (e & 3)][fr] = o[i][e];
+      for (int r = 0; r < 4; ++r) red_o[wave][16 * i + 4 * fh + r][fr] = o[i][r];
   }
   __syncthreads();
 

@@ -26,6 +26,15 @@ __device__ __forceinline__ f32x16 mfma32(const u32x4& a, const u32x4& b, const f
                                                 0, 0, 0);
 }
 
+// 16x16x32 fp16 MFMA, fp32 accumulate.
+//   A operand: lane l holds A[i = l % 16][k = 8 (l / 16) + 0..7]
+//   B operand: lane l holds B[k = 8 (l / 16) + 0..7][j = l % 16]
+//   D:         lane l, register r holds D[i = 4 (l / 16) + r][j = l % 16]
+__device__ __forceinline__ f32x4 mfma16(const u32x4& a, const u32x4& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c,
+                                                0, 0, 0);
+}
+
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float(uint32_t(h) << 16); }
 
 __device__ __forceinline__ float h2f(uint16_t h) { return float(__builtin_bit_cast(_Float16, h)); }
