@@ -51,13 +51,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t cache_rsrc(const uint16_t* bas
                                            0x00020000);
 }
 
-// Two fp32 values -> two fp16 values (round to nearest even), one instruction.
-__device__ __forceinline__ uint32_t pack2h_rne(float lo, float hi) {
-  typedef float f2 __attribute__((ext_vector_type(2)));
-  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{lo, hi}), h2));
-}
-
 // The reference maximum of the online softmax moves only when a tile's
 // maximum exceeds it by more than this (log2 units): weights are then at
 // most 2^8, well inside fp16, and the output rescale is skipped on almost
@@ -358,7 +351,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_kernel(AttnArgs a) {
 // Single-row (decode) attention: one block per (work item, key/value head);
 // the unit is in decode_unit.h.
 template <int DH>
-__global__ __launch_bounds__(kThreads, DH == 64 ? 3 : 2) void decode_attn_kernel(DecodeAttnArgs a) {
+__global__ __launch_bounds__(kThreads, DH == 64 ? 4 : 3) void decode_attn_kernel(DecodeAttnArgs a) {
   __shared__ decode::DecodeSmem<DH> sm;
   const int item = blockIdx.x / a.hkv;
   if (a.n_items_dev && item >= *a.n_items_dev) return;  // a grid sized for a fixed layout

@@ -6,9 +6,9 @@
 // MFMA (G <= 8 valid), so the keys and values of the head are read once for
 // the whole group.  The range is cut into tiles (dec_tile_keys keys); wave w
 // takes tiles w, w + 4, w + 8, ... and keeps its own running softmax state
-// over them.  A tile is loaded as whole lines into registers, two sets deep,
-// and passes through a private LDS image of the wave (no barrier) into MFMA
-// layout.  The four waves' states are merged through LDS.  A row with one
+// over them.  A tile is loaded as whole lines into registers one tile ahead
+// and passes through a private LDS image of the wave (no barrier; keys, then
+// values in their place) into MFMA layout.  The four waves' states are merged through LDS.  A row with one
 // split writes its output directly; otherwise every split publishes its state
 // and the last split of (r, g) to arrive merges them in split order.
 //
@@ -16,9 +16,12 @@
 // fragments fetched straight from the cache put adjacent lanes in different
 // key rows, which occupies a CU's address unit for about 93 cycles per 1 KB
 // against 17 for whole lines, and 32-wide score tiles spend twice the softmax
-// work on columns that hold no query.  A talker step (32 rows of 128 .. 1024
-// keys, 128 CUs, 16 layers) went from 929 to 909 us, one of 128 rows on 160
-// CUs from 2068 to 2013.
+// work on columns that hold no query: a talker step (32 rows of 128 .. 1024
+// keys, 128 CUs, 16 layers) went from 929 to 909 us without, one of 128 rows
+// on 160 CUs from 2068 to 2013.  One register set and half the LDS instead of
+// two sets (four blocks a CU instead of three) and non-temporal loads, which
+// leave the last-level cache to the weights, brought these to 885 and 1913.
+// Five or six blocks a CU spill or gain nothing.
 #pragma once
 
 #include "hs_device.h"
@@ -33,20 +36,24 @@ template <int DH>
 struct DecodeSmem {
   static constexpr int kTile = dec_tile_keys(DH) * DH * 2;  // bytes of a tile's keys, and of its values
   union {
-    uint8_t tile[4][2 * kTile];  // [wave] keys, then values
+    uint8_t tile[4][kTile];  // [wave] a tile's keys, then its values
     struct {
       float red_m[4][8], red_l[4][8];
       float red_o[4][DH][9];  // [wave][d][query head], G <= 8
+      int last;
     };
   };
-  int last;
 };
 
 // Largest and total value over the four lanes that hold one query's keys
-// (lanes l, l ^ 16, l ^ 32, l ^ 48).
+// (lanes l, l ^ 16, l ^ 32, l ^ 48): a swap of a value with itself leaves a
+// lane's own value in one result and its partner's in the other.
 __device__ __forceinline__ float quarter_max(float v) {
-  v = fmaxf(v, __shfl_xor(v, 16, 64));
-  return fmaxf(v, __shfl_xor(v, 32, 64));
+  const uint32_t u = __float_as_uint(v);
+  const auto h = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const uint32_t w = __float_as_uint(fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1])));
+  const auto q = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+  return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
 }
 __device__ __forceinline__ float quarter_sum(float v) {
   v += __shfl_xor(v, 16, 64);
@@ -97,23 +104,23 @@ __device__ __forceinline__ void decode_attn_unit(const DecodeAttnArgs& a, int it
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.vstore + vbase), 0, 0x7ffffff0, 0x00020000);
   const __amdgpu_buffer_rsrc_t zres =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.kstore + kbase), 0, 0, 0x00020000);
-  struct Tile {
+  struct {
     u32x4 k[NL], v[NL];
-  };
-  auto load_k = [&](int i, Tile& tl) {
+  } tl;
+  auto load_k = [&](int i) {
     const __amdgpu_buffer_rsrc_t res = i < my_tiles ? kres : zres;
     const uint32_t so = uint32_t(k_begin + (wave + 4 * i) * TK - key0) * uint32_t(DH * 2);
 #pragma unroll
     for (int l = 0; l < NL; ++l)
-      tl.k[l] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(res, uint32_t(lane * 16 + l * 1024), so, 0));
+      tl.k[l] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(res, uint32_t(lane * 16 + l * 1024), so, kNt));
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto load_v = [&](int i, Tile& tl) {
+  auto load_v = [&](int i) {
     const __amdgpu_buffer_rsrc_t res = i < my_tiles ? vres : zres;
     const uint32_t so = uint32_t(k_begin + (wave + 4 * i) * TK - key0) * uint32_t(DH * 2);
 #pragma unroll
     for (int l = 0; l < NL; ++l)
-      tl.v[l] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(res, uint32_t(lane * 16 + l * 1024), so, 0));
+      tl.v[l] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(res, uint32_t(lane * 16 + l * 1024), so, kNt));
     __builtin_amdgcn_sched_barrier(0);
   };
 
@@ -123,17 +130,9 @@ __device__ __forceinline__ void decode_attn_unit(const DecodeAttnArgs& a, int it
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) qf[kb] = *reinterpret_cast<const u32x4*>(qp + kb * 32);
   }
-  // Register sets: a set is reloaded as soon as its tile is in LDS, keys and
-  // values apart.  At head_dim 64 two sets, at 128 one (16 KB a wave, and two
-  // would spill): 128 KB or more of loads in flight on a full CU either way.
-  constexpr int S = DH == 64 ? 2 : 1;
-  Tile ts[S];
   __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int u = 0; u < S; ++u) {
-    load_k(u, ts[u]);
-    load_v(u, ts[u]);
-  }
+  load_k(0);
+  load_v(0);
   float m_run = -INFINITY, l_run = 0.0f;
   f32x4 o[NDS];
 #pragma unroll
@@ -146,7 +145,7 @@ __device__ __forceinline__ void decode_attn_unit(const DecodeAttnArgs& a, int it
   // 128-byte rows 8 per parity; or of 16 consecutive 64-byte value rows,
   // which need the four rows of each bank quarter apart.
   uint8_t* ks = sm.tile[wave];
-  uint8_t* vs = ks + kTile;
+  uint8_t* vs = ks;  // the values take the keys' place
   auto kphys = [](int r, int c) {
     const int i = ((r >> 3) << 2) | (r & 3);
     return c ^ (DH == 128 ? i : (i >> 1));
@@ -171,14 +170,14 @@ __device__ __forceinline__ void decode_attn_unit(const DecodeAttnArgs& a, int it
   const uint32_t vr = uint32_t(fr * 64 + vphys(fr, fh) * 16);
   // The lanes read each other's chunks: LDS accesses of a wave complete in
   // order, so keeping the program order is enough.
-  auto stage_k = [&](const Tile& tl) {
+  auto stage_k = [&]() {
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int l = 0; l < NL; ++l)
       *reinterpret_cast<u32x4*>(ks + kw[l / kPer] + (l % kPer) * 1024) = tl.k[l];
     asm volatile("" ::: "memory");
   };
-  auto stage_v = [&](const Tile& tl, int ti) {
+  auto stage_v = [&](int ti) {
     asm volatile("" ::: "memory");
     // Values past the range: P is 0 there; keep 0 * garbage out.
     const int v_left = k_end - (k_begin + ti * TK) - 8 * (lane & 3);
@@ -198,11 +197,11 @@ __device__ __forceinline__ void decode_attn_unit(const DecodeAttnArgs& a, int it
   // Online softmax over this wave's tiles, in the exp2 domain.  Score row i
   // of subtile st is key 8 (i / 4) + 4 st + i % 4, which leaves every lane
   // with keys 8 fh .. 8 fh + 7 of its query: the B operand of O^T = V^T P^T.
-  auto do_tile = [&](int i, Tile& tl) {
+  auto do_tile = [&](int i) {
     const int ti = wave + 4 * i;
     const int kv0 = k_begin + ti * TK;
-    stage_k(tl);
-    load_k(i + S, tl);
+    stage_k();
+    load_k(i + 1);
     f32x4 sc[2];
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
@@ -211,25 +210,28 @@ __device__ __forceinline__ void decode_attn_unit(const DecodeAttnArgs& a, int it
       for (int kb = 0; kb < NKB; ++kb)
         sc[st] = mfma16(*reinterpret_cast<const u32x4*>(ks + kr[kb] + st * 4 * DH * 2), qf[kb], sc[st]);
     }
-    const int left = k_end - kv0 - 8 * fh;  // valid keys from the lane's first on
-    float mx = -INFINITY;
+    if (kv0 + TK > k_end) {
+      const int left = k_end - kv0 - 8 * fh;  // valid keys from the lane's first on
 #pragma unroll
-    for (int st = 0; st < 2; ++st)
+      for (int st = 0; st < 2; ++st)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float v = (4 * st + r < left) ? sc[st][r] * a.scale_log2 : -INFINITY;
-        sc[st][r] = v;
-        mx = fmaxf(mx, v);
-      }
-    // Every tile holds at least one valid key, so m_new is finite.
-    const float m_new = fmaxf(m_run, quarter_max(mx));
+        for (int r = 0; r < 4; ++r)
+          if (4 * st + r >= left) sc[st][r] = -INFINITY;
+    }
+    // The maximum is taken on the raw scores (the scale is positive) and the
+    // scale folded into the exponent's FMA.  Every tile holds at least one
+    // valid key, so m_new is finite.
+    float mx = fmaxf(sc[0][0], sc[1][0]);
+#pragma unroll
+    for (int r = 1; r < 4; ++r) mx = fmaxf(mx, fmaxf(sc[0][r], sc[1][r]));
+    const float m_new = fmaxf(m_run, quarter_max(mx) * a.scale_log2);
     const float alpha = exp2_raw(m_run - m_new);  // 0 on the first tile
     float psum = 0.0f;
 #pragma unroll
     for (int st = 0; st < 2; ++st)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float p = exp2_raw(sc[st][r] - m_new);
+        const float p = exp2_raw(fmaf(sc[st][r], a.scale_log2, -m_new));
         sc[st][r] = p;
         psum += p;
       }
@@ -240,23 +242,17 @@ __device__ __forceinline__ void decode_attn_unit(const DecodeAttnArgs& a, int it
 #pragma unroll
       for (int r = 0; r < 4; ++r) o[i][r] *= alpha;
     __builtin_amdgcn_sched_barrier(0);
-    stage_v(tl, ti);
-    load_v(i + S, tl);
+    stage_v(ti);
+    load_v(i + 1);
     u32x4 pf;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) pf[e] = pack2h(sc[e >> 1][2 * (e & 1)], sc[e >> 1][2 * (e & 1) + 1]);
+    for (int e = 0; e < 4; ++e) pf[e] = pack2h_rne(sc[e >> 1][2 * (e & 1)], sc[e >> 1][2 * (e & 1) + 1]);
 #pragma unroll
     for (int i = 0; i < NDS; ++i) o[i] = mfma16(*reinterpret_cast<const u32x4*>(vs + vr + i * 1024), pf, o[i]);
     __builtin_amdgcn_sched_barrier(0);
   };
 
-  // With two sets the last pass may take a tile past the wave's last: zeros,
-  // every score masked, nothing added (the maximum is finite by then).  A
-  // branch around it would cost the loop its exact wait counts.
-  for (int i = 0; i < my_tiles; i += S) {
-#pragma unroll
-    for (int u = 0; u < S; ++u) do_tile(i + u, ts[u]);
-  }
+  for (int i = 0; i < my_tiles; ++i) do_tile(i);
 
   // Merge the four waves.  Lane (fr, fh) holds query column fr; its four
   // lanes share the maximum, each holds part of the sum.  Waves without a

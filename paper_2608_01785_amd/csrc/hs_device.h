@@ -14,6 +14,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kWave = 64;
+constexpr int kNt = 2;  // buffer cache policy nt: data that this launch reads once
 constexpr int kNumXcd = 8;
 constexpr float kF16Max = 65504.0f;
 
@@ -66,6 +67,13 @@ __device__ __forceinline__ uint32_t bf2x_to_h2x(uint32_t u) {
   const float lo = __uint_as_float(u << 16);
   const float hi = __uint_as_float(u & 0xffff0000u);
   return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(lo, hi));
+}
+
+// Two fp32 values -> two fp16 values (round to nearest even), one instruction.
+__device__ __forceinline__ uint32_t pack2h_rne(float lo, float hi) {
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{lo, hi}), h2));
 }
 
 __device__ __forceinline__ u32x4 bf8_to_h8(const u32x4& v) {
