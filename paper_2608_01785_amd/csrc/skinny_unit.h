@@ -3,12 +3,17 @@
 // Decode re-reads every weight for a handful of rows, so the unit streams W
 // rather than reusing it: a block owns a thin strip of weight rows (32, or 64
 // when the epilogue needs RoPE or gate/up pairs), all M rows and one K range.
-// The four waves split the range into interleaved 32-wide panels whose
-// fragments they load straight into registers, several panels in flight per
-// wave, so no wave waits on another until the end, where partial accumulators
-// are summed through LDS and the fused epilogues run (residual add into fp32,
-// SwiGLU, or RoPE + key/value store).  A K split publishes fp32 partial sums;
-// the last split of a strip to arrive adds them in split order.
+// The four waves split the range into interleaved stages of 64; a wave loads a
+// stage's weights as whole lines into registers, several stages ahead, and
+// passes them through an LDS image of its own into MFMA layout, so no wave
+// waits on another until the end, where partial accumulators are summed
+// through LDS and the fused epilogues run (residual add into fp32, SwiGLU, or
+// RoPE + key/value store).  A K split publishes fp32 partial sums; the last
+// split of a strip to arrive adds them in split order.
+//
+// What bounds it is memory, once the loads are whole lines: fragments fetched
+// straight from memory put adjacent lanes in different weight rows, which
+// costs a CU's address unit about 93 cycles per 1 KB against 17.
 //
 // Weights are bf16 row-major or prepared fp16 panel-major ([K / 32][N][32]).
 // The weight strip is the MFMA A operand and activation rows the B operand, so
@@ -54,16 +59,19 @@ __device__ __forceinline__ uint32_t strip_row(int tile, int r, int ffn) {
   }
 }
 
-// LDS of one block: the cross-wave reduction buffer and an arrival flag.
+// LDS of one block: the waves' stage images or the cross-wave reduction
+// buffer, and an arrival flag.  A stage image holds two 32-wide panels of
+// 32 NS rows.
 template <int NS, int MT>
 struct SkinnyShape {
+  static constexpr int IMAGE = 2 * NS * 32 * 64;
   static constexpr int RED = 4 * NS * MT * 16 * 64 * 4;
-  static constexpr int SMEM = RED + 16;
+  static constexpr int SMEM = (RED > 4 * IMAGE ? RED : 4 * IMAGE) + 16;
 };
 
-// 32-wide K panels per chunk (a chunk is 2 (NS + MT) fragment loads).
-template <int NS, int MT>
-constexpr int skinny_chunk() { return NS + MT <= 3 ? 2 : 1; }
+// Stages in flight per wave: with four the talker step took 891 us against
+// 880 with two (more registers and instructions ahead of the first product).
+constexpr int kSets = 2;
 
 // One weight strip (`tile`) and one K split (`ks`) of a skinny GEMM, by one
 // block of kThreads threads, in LDS `smem` (SkinnyShape::SMEM bytes, 1 KB
@@ -71,7 +79,7 @@ constexpr int skinny_chunk() { return NS + MT <= 3 ? 2 : 1; }
 template <int EPI, int DH, bool W_F16, int NS, int MT>
 __device__ __forceinline__ void skinny_unit(const GemmArgs& a, int tile, int ks, uint8_t* smem) {
   constexpr int NR = 32 * NS;                 // weight rows per block
-  constexpr int CH = skinny_chunk<NS, MT>();
+  constexpr int S = kSets;
   constexpr int SMEM = SkinnyShape<NS, MT>::SMEM;
   static_assert(SMEM <= kLdsBytes, "LDS");
 
@@ -79,29 +87,30 @@ __device__ __forceinline__ void skinny_unit(const GemmArgs& a, int tile, int ks,
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int fr = lane & 31, fh = lane >> 5;
   const int n_split = a.n_split;
-  // Folded RMSNorm: this lane's row's partial sums of squares, loaded now and
-  // summed in the epilogue (wave w owns rows 32 w .. 32 w + 31 there).  Rows
-  // past M fall outside the buffer range and read zero.
-  constexpr int kPre = (EPI == EPI_RESID) ? 1 : kSkinnyMaxNormParts / 4;
+  const int m_own = wave * 32 + fr;
+  const bool row_own = wave < MT && m_own < a.M;
+  // Folded RMSNorm: this lane's row's partial sums of squares, half of them in
+  // each of the row's two lanes, loaded now and summed in the epilogue (wave w
+  // owns rows 32 w .. 32 w + 31 there).  Rows past M fall outside the buffer
+  // range and read zero.
+  constexpr int kPre = (EPI == EPI_RESID) ? 1 : kSkinnyMaxNormParts / 8;
   u32x4 pre[kPre];
   const bool want_rs = EPI != EPI_RESID && a.row_sumsq && wave < MT;
   if (want_rs) {
     const __amdgpu_buffer_rsrc_t pr = make_rsrc(a.row_sumsq, uint32_t(a.M) * a.row_parts * 4);
-    const uint32_t row_off = uint32_t((wave * 32 + fr) * a.row_parts) * 4;
+    const uint32_t row_off = uint32_t(m_own * a.row_parts + 4 * fh) * 4;
 #pragma unroll
     for (int u = 0; u < kPre; ++u)
-      if (4 * u < a.row_parts)
-        pre[u] = __builtin_amdgcn_raw_buffer_load_b128(pr, row_off + uint32_t(u * 16), 0, 0);
+      if (8 * u < a.row_parts)
+        pre[u] = __builtin_amdgcn_raw_buffer_load_b128(pr, row_off + uint32_t(u * 32), 0, 0);
   }
   // Operands of the epilogue that do not depend on the product, loaded now
   // so that they are in registers by then (wave w owns rows 32 w .. 32 w + 31
   // there): RESID the residual and the next norm's gains; QKV the row's
   // position, cache offsets and RoPE table entries (issued after the first
-  // chunk's loads, see below).
+  // stages' loads, see below).
   f32x4 res_pre[EPI == EPI_RESID ? NS : 1][4];
   f32x4 gain_pre[EPI == EPI_RESID ? NS : 1][4];
-  const int m_own = wave * 32 + fr;
-  const bool row_own = wave < MT && m_own < a.M;
   if constexpr (EPI == EPI_RESID) {
     if (row_own) {
 #pragma unroll
@@ -140,34 +149,49 @@ __device__ __forceinline__ void skinny_unit(const GemmArgs& a, int tile, int ks,
   const __amdgpu_buffer_rsrc_t xres =
       make_rsrc(a.A, a.k8_rows ? uint32_t(a.K) * uint32_t(a.k8_rows) * 2 : uint32_t(a.M) * row_bytes);
 
-  // Fragments go from memory straight into registers in MFMA operand layout.
-  // The split's K range is cut into 32-wide panels; wave w takes panels w,
-  // w + 4, w + 8, ... in chunks of CH panels and loads chunk c + 1 while it
-  // multiplies chunk c.  A panel past the range is read through an empty
-  // buffer resource, so it returns zeros and moves no data.
+  // Wave w takes stages w, w + 4, w + 8, ... of the split, S of them in
+  // flight.  A stage past the range is read through an empty buffer resource:
+  // zeros, no traffic, products that add nothing, and the same loads in every
+  // iteration, so the wait counts stay exact.
   //   weight fragment (A operand): rows strip_row(i * 32 + fr), K 16 s + 8 fh .. + 7
   //   activation fragment (B operand): rows j * 32 + fr, the same K
+  // Every weight load of a wave covers 1 KB in runs of 64 bytes or more: 16
+  // rows of one 32-wide panel of prepared weights, or 8 rows x 128 bytes.
   static_assert(NS <= 2 && MT <= 4, "fragment slots");
+  constexpr int WL = 4 * NS;  // 1 KB weight loads of a stage
   const __amdgpu_buffer_rsrc_t zres = make_rsrc(a.W, 0);
-  uint32_t w_off[NS], x_off[MT];
+  const uint32_t panel_bytes = w_rows * 64;
+  uint8_t* image = smem + wave * SkinnyShape<NS, MT>::IMAGE;
+  // 16-byte chunk c of row r of panel q sits in image row r ^ q at physical
+  // chunk c ^ (r / 4 % 4): a 16-lane pass of fragment reads takes one logical
+  // chunk of 16 consecutive 64-byte rows, which need the four rows of each
+  // bank quarter apart; eight writing lanes hold two rows of a panel, or one
+  // row of both.
+  auto phys = [](int q, int r, int c) { return uint32_t((q * NS * 32 + (r ^ q)) * 64 + (c ^ ((r >> 2) & 3)) * 16); };
+  uint32_t w_off[WL], w_lds[WL];
 #pragma unroll
-  for (int i = 0; i < NS; ++i) {
-    const uint32_t r = strip_row<EPI, NR, DH>(tile, i * 32 + fr, a.ffn);
-    w_off[i] = (W_F16 ? r * 64u : r * row_bytes) + uint32_t(fh * 16);
+  for (int l = 0; l < WL; ++l) {
+    if constexpr (W_F16) {
+      const int q = l & 1, r = 16 * (l >> 1) + (lane >> 2), c = lane & 3;
+      w_off[l] = strip_row<EPI, NR, DH>(tile, r, a.ffn) * 64u + uint32_t(q) * panel_bytes + uint32_t(c * 16);
+      w_lds[l] = phys(q, r, c);
+    } else {
+      const int r = 8 * l + (lane >> 3), c = lane & 7;
+      w_off[l] = strip_row<EPI, NR, DH>(tile, r, a.ffn) * row_bytes + uint32_t(c * 16);
+      w_lds[l] = phys(c >> 2, r, c & 3);
+    }
   }
-  // Activations row-major: a step is 32 bytes along the row, a panel 64.
-  // k-group-major (k8_rows padded rows): a fragment is 512 contiguous bytes,
-  // a step 2 k-groups and a panel 4.
+  const uint32_t w_stage = W_F16 ? 2 * panel_bytes : 128u;
+  // Activations row-major: a step is 32 bytes along the row.  k-group-major
+  // (k8_rows padded rows): a fragment is 512 contiguous bytes, a step 2
+  // k-groups.
+  uint32_t x_off[MT];
   const int k8 = a.k8_rows;
 #pragma unroll
   for (int j = 0; j < MT; ++j)
     x_off[j] = k8 ? uint32_t((fh * k8 + j * 32 + fr) * 16) : uint32_t(j * 32 + fr) * row_bytes + uint32_t(fh * 16);
   const uint32_t x_step = k8 ? uint32_t(2 * k8 * 16) : 32u;
-  const uint32_t x_panel = k8 ? uint32_t(4 * k8 * 16) : 64u;
-  const uint32_t panel_bytes = w_rows * 64;
-  const int n_panels = 2 * KT;
-  const int my_panels = n_panels > wave ? (n_panels - wave + 3) / 4 : 0;
-  const int n_chunks = (my_panels + CH - 1) / CH;
+  const int my_stages = KT > wave ? (KT - wave + 3) / 4 : 0;
 
   f32x16 acc[NS][MT];
 #pragma unroll
@@ -177,49 +201,65 @@ __device__ __forceinline__ void skinny_unit(const GemmArgs& a, int tile, int ks,
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-  struct Chunk {
-    u32x4 w[CH][2][NS];
-    u32x4 x[CH][2][MT];
+  struct Stage {
+    u32x4 w[WL];
+    u32x4 x[4][MT];
   };
-  auto load_chunk = [&](int c, Chunk& b) {
+  auto load_w = [&](int i, Stage& b) {
+    const __amdgpu_buffer_rsrc_t wr = i < my_stages ? wres : zres;
+    const uint32_t P = uint32_t(kt0 + wave + 4 * i);  // stage of the matrix
 #pragma unroll
-    for (int q = 0; q < CH; ++q) {
-      const int p = wave + 4 * (c * CH + q);  // panel of this split
-      const bool ok = p < n_panels;
-      const __amdgpu_buffer_rsrc_t wr = ok ? wres : zres;
-      const __amdgpu_buffer_rsrc_t xr = ok ? xres : zres;
-      const uint32_t P = uint32_t(2 * kt0 + p);  // panel of the matrix
-      const uint32_t wso = W_F16 ? P * panel_bytes : P * 64u;
+    for (int l = 0; l < WL; ++l) b.w[l] = __builtin_amdgcn_raw_buffer_load_b128(wr, w_off[l], P * w_stage, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto load_x = [&](int i, Stage& b) {
+    const __amdgpu_buffer_rsrc_t xr = i < my_stages ? xres : zres;
+    const uint32_t P = uint32_t(kt0 + wave + 4 * i);
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int i = 0; i < NS; ++i)
-          b.w[q][s][i] = __builtin_amdgcn_raw_buffer_load_b128(wr, w_off[i] + 32 * s, wso, 0);
+      for (int j = 0; j < MT; ++j)
+        b.x[s][j] = __builtin_amdgcn_raw_buffer_load_b128(xr, x_off[j] + x_step * s, P * 4 * x_step, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // A stage's weights through the wave's image.  The lanes read each other's
+  // chunks: LDS accesses of a wave complete in order, so keeping the program
+  // order is enough.
+  struct Frag {
+    u32x4 w[4][NS];
+  };
+  auto pass_w = [&](const Stage& b, Frag& f) {
+    asm volatile("" ::: "memory");
 #pragma unroll
-        for (int j = 0; j < MT; ++j)
-          b.x[q][s][j] = __builtin_amdgcn_raw_buffer_load_b128(xr, x_off[j] + x_step * s, P * x_panel, 0);
+    for (int l = 0; l < WL; ++l) *reinterpret_cast<u32x4*>(image + w_lds[l]) = b.w[l];
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int n = 0; n < NS; ++n)
+        f.w[s][n] = *reinterpret_cast<const u32x4*>(image + phys(s >> 1, fr, 2 * (s & 1) + fh) + n * 32 * 64);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto mma = [&](const Stage& b, const Frag& f) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int n = 0; n < NS; ++n) {
+        const u32x4 wh = W_F16 ? f.w[s][n] : bf8_to_h8(f.w[s][n]);
+#pragma unroll
+        for (int j = 0; j < MT; ++j) acc[n][j] = mfma32(wh, b.x[s][j], acc[n][j]);
       }
-    }
-  };
-  auto mma_chunk = [&](const Chunk& b) {
-#pragma unroll
-    for (int q = 0; q < CH; ++q)
-#pragma unroll
-      for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int i = 0; i < NS; ++i) {
-          const u32x4 wh = W_F16 ? b.w[q][s][i] : bf8_to_h8(b.w[q][s][i]);
-#pragma unroll
-          for (int j = 0; j < MT; ++j) acc[i][j] = mfma32(wh, b.x[q][s][j], acc[i][j]);
-        }
+    __builtin_amdgcn_sched_barrier(0);
   };
 
-  // Two register sets.  Chunk 0 is always loaded (a wave without panels
-  // reads zeros); later chunks are loaded only when they hold panels of this
-  // wave, so the compiler's wait counts stay exact, and the scheduling
-  // barriers keep each chunk's loads ahead of the previous chunk's MFMAs.
-  Chunk b0, b1;
-  load_chunk(0, b0);
+  Stage st[S];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < S; ++u) {
+    load_w(u, st[u]);
+    load_x(u, st[u]);
+  }
   // QKV: the RoPE table entries of this lane's dimension pairs and, with a
   // bias, the bias of its columns (registers 4 g + e: dimension
   // 16 sub + 8 g + 4 fh + e, registers 4 (g + 2) + e: that plus DH / 2).
@@ -246,27 +286,20 @@ __device__ __forceinline__ void skinny_unit(const GemmArgs& a, int tile, int ks,
         load_bf16x4(bp + 8 * g + DH / 2, &bias_pre[4 * (g + 2)]);
       }
     }
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  int ch = 0;
-  for (; ch + 2 < n_chunks; ch += 2) {
-    load_chunk(ch + 1, b1);
-    __builtin_amdgcn_sched_barrier(0);
-    mma_chunk(b0);
-    __builtin_amdgcn_sched_barrier(0);
-    load_chunk(ch + 2, b0);
-    __builtin_amdgcn_sched_barrier(0);
-    mma_chunk(b1);
     __builtin_amdgcn_sched_barrier(0);
   }
-  if (n_chunks - ch == 2) {
-    load_chunk(ch + 1, b1);
-    __builtin_amdgcn_sched_barrier(0);
-    mma_chunk(b0);
-    __builtin_amdgcn_sched_barrier(0);
-    mma_chunk(b1);
-  } else if (n_chunks - ch == 1) {
-    mma_chunk(b0);
+  // The next stage's weights pass through LDS ahead of this one's products.
+  Frag f[2];
+  pass_w(st[0], f[0]);
+  load_w(S, st[0]);
+  for (int i = 0; i < my_stages; i += S) {
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+      pass_w(st[(u + 1) % S], f[(u + 1) & 1]);
+      load_w(i + u + 1 + S, st[(u + 1) % S]);
+      mma(st[u], f[u & 1]);
+      load_x(i + u + S, st[u]);
+    }
   }
 
   // Sum the four waves' partial accumulators through LDS ([wave][i][j][lane]
@@ -380,24 +413,23 @@ __device__ __forceinline__ void skinny_unit(const GemmArgs& a, int tile, int ks,
     }
     return;
   } else {
-    if (!owner || m >= a.M) return;
+    if (!owner) return;
     if (want_rs) {
       float sum = 0.0f;
 #pragma unroll
       for (int u = 0; u < kPre; ++u) {
-        if (4 * u >= a.row_parts) break;
+        if (8 * u >= a.row_parts) break;
         const f32x4 f = __builtin_bit_cast(f32x4, pre[u]);
-        sum += f[0];
-        sum += f[1];
-        sum += f[2];
-        sum += f[3];
+        if (8 * u + 4 * fh < a.row_parts) sum += f[0] + f[1] + f[2] + f[3];
       }
+      sum += __shfl_xor(sum, 32, 64);
       const float rs = rsqrtf(sum / float(a.K) + a.eps);
 #pragma unroll
       for (int i = 0; i < NS; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) c[i][r] *= rs;
     }
+    if (m >= a.M) return;
     if constexpr (EPI == EPI_QKV) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) c[0][r] += bias_pre[r];
