@@ -578,12 +578,7 @@ hipError_t launch_one(const GemmArgs& a, int max_blocks, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_gemm(int epi, const GemmArgs& a, int max_blocks, hipStream_t s) {
-  if (a.M <= 0) return hipSuccess;
-  if (a.K < BK * kUnroll || a.K % (BK * kUnroll) != 0) return hipErrorInvalidValue;
-  if (a.sumsq_out || a.scaled_out || a.row_sumsq) return hipErrorInvalidValue;
-  const int tile = gemm_tile_choice(a.M, a.n_tiles_n * 256, a.K, max_blocks);
-  if (tile >= 0) return launch_gemm_tile(epi, a, tile, s);
+hipError_t launch_gemm_persistent(int epi, const GemmArgs& a, int max_blocks, hipStream_t s) {
   switch (epi) {
     case EPI_RESID: return launch_one<EPI_RESID, 128>(a, max_blocks, s);
     case EPI_SWIGLU: return launch_one<EPI_SWIGLU, 128>(a, max_blocks, s);
@@ -594,6 +589,14 @@ hipError_t launch_gemm(int epi, const GemmArgs& a, int max_blocks, hipStream_t s
                         : launch_one<EPI_QKV, 128>(a, max_blocks, s);
     default: return hipErrorInvalidValue;
   }
+}
+
+hipError_t launch_gemm(int epi, const GemmArgs& a, int max_blocks, hipStream_t s) {
+  if (a.M <= 0) return hipSuccess;
+  if (a.K < BK * kUnroll || a.K % (BK * kUnroll) != 0) return hipErrorInvalidValue;
+  if (a.sumsq_out || a.scaled_out || a.row_sumsq) return hipErrorInvalidValue;
+  const int tile = gemm_tile_choice(a.M, a.n_tiles_n * 256, a.K, max_blocks);
+  return tile >= 0 ? launch_gemm_tile(epi, a, tile, s) : launch_gemm_persistent(epi, a, max_blocks, s);
 }
 
 }  // namespace hs

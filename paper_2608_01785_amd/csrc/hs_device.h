@@ -264,11 +264,13 @@ __device__ __forceinline__ int rope_pos(const Args& a, int m, int j) {
   return a.pos[c * a.pos_stride + m];
 }
 
-// One rotation pair: (lo, hi) -> (lo cos - hi sin, hi cos + lo sin), with the
-// roundings spelled out so that every GEMM gives the same bits.
+// One rotation pair of the prefill GEMMs: (lo, hi) -> (lo cos - hi sin,
+// hi cos + lo sin), with the roundings spelled out so that the persistent
+// kernel and every tile shape give the same bits.  (The skinny GEMM's
+// epilogue rounds lo sin instead of hi cos in the second value.)
 __device__ __forceinline__ void rope_rotate(float lo, float hi, float2 cs, float& rl, float& rh) {
   rl = fmaf(lo, cs.x, -(hi * cs.y));
-  rh = fmaf(hi, cs.x, lo * cs.y);
+  rh = fmaf(lo, cs.y, hi * cs.x);
 }
 
 __device__ __forceinline__ float wave_max(float v) {

@@ -74,6 +74,7 @@ struct GemmArgs {
 // max_blocks: the budget's CUs.  Runs the persistent kernel or, where
 // gemm_tile_choice() says so, a small-tile shape (the same bits).
 hipError_t launch_gemm(int epi, const GemmArgs& a, int max_blocks, hipStream_t s);
+hipError_t launch_gemm_persistent(int epi, const GemmArgs& a, int max_blocks, hipStream_t s);
 hipError_t launch_gemm_tile(int epi, const GemmArgs& a, int tile, hipStream_t s);
 
 // Decode-sized GEMMs (M <= kSkinnyMaxRows): thin weight strips, K split

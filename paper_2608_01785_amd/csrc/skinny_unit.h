@@ -457,8 +457,8 @@ __device__ __forceinline__ void skinny_unit(const GemmArgs& a, int tile, int ks,
         for (int e = 0; e < 4; ++e) {
           const float2 cs = rope_pre[4 * g + e];
           const float lo = c[0][4 * g + e], hi = c[0][4 * (g + 2) + e];
-          rl[e] = lo * cs.x - hi * cs.y;
-          rh[e] = hi * cs.x + lo * cs.y;
+          rl[e] = fmaf(lo, cs.x, -(hi * cs.y));
+          rh[e] = fmaf(hi, cs.x, lo * cs.y);
         }
         uint16_t* dst = (head < a.hq) ? a.q + (int64_t(m) * a.hq + head) * DH
                                       : a.kstore + qkv_koff + int64_t(head - a.hq) * a.kv_head_stride;
