@@ -4,10 +4,10 @@
 // rather than reusing it: a block owns a thin strip of weight rows (32, or 64
 // when the epilogue needs RoPE or gate/up pairs), all M rows and one K range.
 // The four waves split the range into interleaved stages of 64; a wave loads a
-// stage's weights as whole lines into registers, several stages ahead, and
-// passes them through an LDS image of its own into MFMA layout, so no wave
-// waits on another until the end, where partial accumulators are summed
-// through LDS and the fused epilogues run (residual add into fp32, SwiGLU, or
+// stage's weights as whole lines into registers, two stages ahead, and passes
+// them through an LDS image of its own into MFMA layout, so no wave waits on
+// another until the end, where partial accumulators are summed through LDS
+// and the fused epilogues run (residual add into fp32, SwiGLU, or
 // RoPE + key/value store).  A K split publishes fp32 partial sums; the last
 // split of a strip to arrive adds them in split order.
 //
@@ -20,6 +20,8 @@
 // each lane of a 32x32 accumulator owns one activation row and 4 consecutive
 // output columns per register group.
 #pragma once
+
+#include <type_traits>
 
 #include "hs_device.h"
 #include "hs_kernels.h"
@@ -69,9 +71,7 @@ struct SkinnyShape {
   static constexpr int SMEM = (RED > 4 * IMAGE ? RED : 4 * IMAGE) + 16;
 };
 
-// Stages in flight per wave: with four the talker step took 891 us against
-// 880 with two (more registers and instructions ahead of the first product).
-constexpr int kSets = 2;
+constexpr int kSets = 2;  // stages in flight per wave, and walked per iteration
 
 // One weight strip (`tile`) and one K split (`ks`) of a skinny GEMM, by one
 // block of kThreads threads, in LDS `smem` (SkinnyShape::SMEM bytes, 1 KB
@@ -149,9 +149,10 @@ __device__ __forceinline__ void skinny_unit(const GemmArgs& a, int tile, int ks,
   const __amdgpu_buffer_rsrc_t xres =
       make_rsrc(a.A, a.k8_rows ? uint32_t(a.K) * uint32_t(a.k8_rows) * 2 : uint32_t(a.M) * row_bytes);
 
-  // Wave w takes stages w, w + 4, w + 8, ... of the split, S of them in
-  // flight.  A stage past the range is read through an empty buffer resource:
-  // zeros, no traffic, products that add nothing, and the same loads in every
+  // Wave w takes stages w, w + 4, w + 8, ... of the split, in pairs, S of them
+  // in flight.  A stage past the range (the second of an odd last pair, both
+  // of a wave without stages) is read through an empty buffer resource: zeros,
+  // no traffic, products that add nothing, and the same loads in every
   // iteration, so the wait counts stay exact.
   //   weight fragment (A operand): rows strip_row(i * 32 + fr), K 16 s + 8 fh .. + 7
   //   activation fragment (B operand): rows j * 32 + fr, the same K
@@ -222,35 +223,42 @@ __device__ __forceinline__ void skinny_unit(const GemmArgs& a, int tile, int ks,
         b.x[s][j] = __builtin_amdgcn_raw_buffer_load_b128(xr, x_off[j] + x_step * s, P * 4 * x_step, 0);
     __builtin_amdgcn_sched_barrier(0);
   };
-  // A stage's weights through the wave's image.  The lanes read each other's
-  // chunks: LDS accesses of a wave complete in order, so keeping the program
-  // order is enough.
-  struct Frag {
-    u32x4 w[4][NS];
-  };
-  auto pass_w = [&](const Stage& b, Frag& f) {
+  // Stage i: its weights through the wave's image, the loads of stage i + S
+  // into the registers it leaves (`next`: its pair has one), its products.
+  // Nothing here waits for stage i + 1, so a wave with four stages (K = 1024)
+  // takes two memory latencies.  Passing stage i + 1 through LDS ahead of
+  // stage i's products hides the LDS latency, but then the activations of
+  // stage i + 2 are not asked for before the weights of stage i + 1 are
+  // there: three latencies, and loads past the end besides (talker step of
+  // one row, two layers, 64 CUs: 83.3 us, now 76.7; 16 layers of 32 rows on
+  // 128 CUs 880, now 850; one thinker layer of 4 rows 195, now 192).
+  // The lanes read each other's chunks: LDS accesses of a wave complete in
+  // order, so keeping the program order is enough.
+  auto stage = [&](int i, Stage& b, auto next) {
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int l = 0; l < WL; ++l) *reinterpret_cast<u32x4*>(image + w_lds[l]) = b.w[l];
     asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (decltype(next)::value) load_w(i + S, b);
+    u32x4 f[4][NS];
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int n = 0; n < NS; ++n)
-        f.w[s][n] = *reinterpret_cast<const u32x4*>(image + phys(s >> 1, fr, 2 * (s & 1) + fh) + n * 32 * 64);
+        f[s][n] = *reinterpret_cast<const u32x4*>(image + phys(s >> 1, fr, 2 * (s & 1) + fh) + n * 32 * 64);
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-  };
-  auto mma = [&](const Stage& b, const Frag& f) {
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int n = 0; n < NS; ++n) {
-        const u32x4 wh = W_F16 ? f.w[s][n] : bf8_to_h8(f.w[s][n]);
+        const u32x4 wh = W_F16 ? f[s][n] : bf8_to_h8(f[s][n]);
 #pragma unroll
         for (int j = 0; j < MT; ++j) acc[n][j] = mfma32(wh, b.x[s][j], acc[n][j]);
       }
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (decltype(next)::value) load_x(i + S, b);
   };
 
   Stage st[S];
@@ -288,19 +296,15 @@ __device__ __forceinline__ void skinny_unit(const GemmArgs& a, int tile, int ks,
     }
     __builtin_amdgcn_sched_barrier(0);
   }
-  // The next stage's weights pass through LDS ahead of this one's products.
-  Frag f[2];
-  pass_w(st[0], f[0]);
-  load_w(S, st[0]);
-  for (int i = 0; i < my_stages; i += S) {
-#pragma unroll
-    for (int u = 0; u < S; ++u) {
-      pass_w(st[(u + 1) % S], f[(u + 1) & 1]);
-      load_w(i + u + 1 + S, st[(u + 1) % S]);
-      mma(st[u], f[u & 1]);
-      load_x(i + u + S, st[u]);
-    }
+  constexpr std::true_type more{};
+  constexpr std::false_type done{};
+  int i = 0;
+  for (; i + S < my_stages; i += S) {
+    stage(i, st[0], more);
+    stage(i + 1, st[1], more);
   }
+  stage(i, st[0], done);
+  stage(i + 1, st[1], done);
 
   // Sum the four waves' partial accumulators through LDS ([wave][i][j][lane]
   // images of 16 floats, moved 16 bytes at a time); wave w then owns row
