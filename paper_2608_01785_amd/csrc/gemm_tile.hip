@@ -198,7 +198,7 @@ __global__ __launch_bounds__(WN * WM * 64, 2) void tile_kernel(GemmArgs a) {
   const int tiles_n = a.n_tiles_n * 256 / BN;
   const int L = int(blockIdx.x % kNumXcd) * int(gridDim.x / kNumXcd) + int(blockIdx.x / kNumXcd);
   if (L >= tiles_m * tiles_n) return;
-  LaunchClock clk;
+  TileClock clk;
   clk.begin(a.clock);
   const int per_group = kGroupM * tiles_n;
   const int first_m = (L / per_group) * kGroupM;

@@ -227,7 +227,7 @@ __device__ __forceinline__ void h2x_to_f(uint32_t u, float& lo, float& hi) {
 // Launch clock record (timing mode only): the first lane of block 0 reads the
 // shader-clock counter (s_memtime, counts core clock cycles) and the
 // constant-rate counter (s_memrealtime) at entry and exit and stores the four
-// values with one vector store, so the host can derive the sustained clock.
+// values, so the host can derive the sustained clock.
 struct LaunchClock {
   uint64_t c0 = 0, w0 = 0;
   __device__ __forceinline__ void begin(const uint64_t* out) {
@@ -244,6 +244,32 @@ struct LaunchClock {
       out[1] = w0;
       out[2] = c1;
       out[3] = w1;
+    }
+  }
+};
+
+// The same where a block lives for one tile of many: the blocks of XCD 0 add
+// their cycles and ticks up (from zero), so the record holds the clock
+// averaged over the tiles, from the first round to the last.  The counters of
+// two CUs are not comparable, so a start and an end of different blocks are
+// not.
+struct TileClock {
+  uint64_t c0 = 0, w0 = 0;
+  __device__ __forceinline__ bool mine(const uint64_t* out) const {
+    return out && blockIdx.x % kNumXcd == 0 && threadIdx.x == 0;
+  }
+  __device__ __forceinline__ void begin(const uint64_t* out) {
+    if (mine(out)) {
+      c0 = __builtin_amdgcn_s_memtime();
+      w0 = __builtin_amdgcn_s_memrealtime();
+    }
+  }
+  __device__ __forceinline__ void end(uint64_t* out) const {
+    if (mine(out)) {
+      const uint64_t c1 = __builtin_amdgcn_s_memtime();
+      const uint64_t w1 = __builtin_amdgcn_s_memrealtime();
+      atomicAdd(reinterpret_cast<unsigned long long*>(out + 2), static_cast<unsigned long long>(c1 - c0));
+      atomicAdd(reinterpret_cast<unsigned long long*>(out + 3), static_cast<unsigned long long>(w1 - w0));
     }
   }
 };

@@ -66,7 +66,8 @@ struct GemmArgs {
   // Skinny GEMM only: A, out and scaled_out are k-group-major with this many
   // padded rows (skinny_k8_rows(M)); 0 = row-major.
   int k8_rows;
-  // Timing mode: four counters of the launch (see LaunchClock), or null.
+  // Timing mode: four counters of the launch, zero on entry (see LaunchClock
+  // and TileClock), or null.
   uint64_t* clock;
 };
 

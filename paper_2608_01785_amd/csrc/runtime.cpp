@@ -1273,16 +1273,20 @@ hs_status hs_timing_read_clock(hs_context* ctx, int32_t kind, double* mhz, int32
   HIP_TRY(hipMemcpy(c.data(), ctx->clock_buf, c.size() * sizeof(uint64_t), hipMemcpyDeviceToHost));
   int wall_khz = 0;
   HIP_TRY(hipDeviceGetAttribute(&wall_khz, hipDeviceAttributeWallClockRate, ctx->device));
-  double cycles = 0.0, ticks = 0.0;
+  // Weighted by the launches' times: a record's ticks are one block's, or the
+  // sum over some of them.
+  double mhz_ms = 0.0, total_ms = 0.0;
   int32_t n = 0;
   for (size_t i = 0; i < ctx->recs.size(); ++i) {
     const uint64_t* v = &c[4 * i];
     if (ctx->recs[i].kind != kind || v[3] <= v[1] || v[2] <= v[0]) continue;
-    cycles += double(v[2] - v[0]);
-    ticks += double(v[3] - v[1]);
+    float ms = 0.0f;
+    HIP_TRY(hipEventElapsedTime(&ms, ctx->recs[i].a, ctx->recs[i].b));
+    mhz_ms += double(ms) * double(v[2] - v[0]) / double(v[3] - v[1]) * (double(wall_khz) / 1e3);
+    total_ms += double(ms);
     ++n;
   }
-  if (n && ticks > 0.0) *mhz = cycles / ticks * (double(wall_khz) / 1e3);
+  if (n && total_ms > 0.0) *mhz = mhz_ms / total_ms;
   *n_launches = n;
   return HS_OK;
 }
