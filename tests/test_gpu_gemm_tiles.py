@@ -1,9 +1,12 @@
-"""The small-tile GEMMs against the reference and, bit for bit, across budgets.
+"""Prefill layers and denoising steps against the reference and, bit for bit, across budgets.
 
-Each budget picks its own tile shapes for a layer's four projections, so equal
-outputs at every budget compare the shapes with each other and with the
-persistent kernel; one of them is compared with the float64 reference.  Row
-counts sit at the edges of 64-, 96-, 128-, 160- and 192-row tiles.
+Each budget sends a layer's four projections to kernels of its own choice, so
+equal outputs at every budget compare whole calls whose kernels differ; one of
+them is compared with the float64 reference.  Which kernels the cases reach is
+pinned on the CPU in test_gemm_choice.py: every epilogue meets the persistent
+kernel and at least four tile shapes, not all seven (test_gpu_gemm_kernels.py
+names each kernel for each epilogue).  Row counts sit at the edges of 64-, 96-,
+128-, 160- and 192-row tiles and past the 256-row tiles' first sizes.
 """
 import numpy as np
 import pytest
@@ -29,10 +32,14 @@ def env():
     ctx.close()
 
 
-@pytest.mark.parametrize("shape_name,rows,fmt", [
+LAYER_CASES = [
     ("talker", 129, "f16"), ("talker", 193, "bf16"), ("talker", 257, "f16"), ("talker", 385, "bf16"),
-    ("talker", 641, "f16"), ("talker", 1100, "bf16"), ("tiny", 191, "f16"), ("tiny", 2305, "bf16"),
-])
+    ("talker", 641, "f16"), ("talker", 1100, "bf16"), ("talker", 3330, "f16"), ("tiny", 191, "f16"),
+    ("tiny", 2305, "bf16"),
+]
+
+
+@pytest.mark.parametrize("shape_name,rows,fmt", LAYER_CASES)
 def test_layer_tiles(env, shape_name, rows, fmt):
     torch, ctx = env
     from paper_2608_01785_amd import binding
@@ -63,7 +70,11 @@ def test_layer_tiles(env, shape_name, rows, fmt):
         np.testing.assert_array_equal(got, first)
 
 
-@pytest.mark.parametrize("rows,fmt", [(65, "f16"), (161, "bf16"), (449, "f16"), (1025, "bf16")])
+DIT_BUDGETS = (64, 96, 160, 192)   # the complements of 192, 160, 96 and 64
+DIT_CASES = [(65, "f16"), (161, "bf16"), (449, "f16"), (800, "bf16"), (1025, "bf16"), (3073, "f16"), (3329, "bf16")]
+
+
+@pytest.mark.parametrize("rows,fmt", DIT_CASES)
 def test_dit_tiles(env, rows, fmt):
     torch, ctx = env
     from paper_2608_01785_amd import binding
@@ -79,7 +90,7 @@ def test_dit_tiles(env, rows, fmt):
         wdev = prepare_dit_f16(ctx, wdev)
     ws = torch.empty(binding.hs_dit_workspace_size(shape, rows, 2), dtype=torch.uint8, device="cuda")
     first = None
-    for b in (64, 96, 160, 192):   # the complements of 192, 160, 96 and 64
+    for b in DIT_BUDGETS:
         log(f"[dit {rows} rows {fmt}] {b} CUs")
         y = torch.full((rows, shape.hidden), float("nan"), dtype=torch.float32, device="cuda")
         xd, cd = to_device(x), torch.from_numpy(cond).to("cuda")

@@ -81,6 +81,47 @@ def test_prefill_with_mrope_positions(env, shape_name, lengths, n_img):
     np.testing.assert_array_equal(y_eq, y.cpu().numpy())
 
 
+PERSISTENT_ROWS = 1100   # on 64 CUs; test_gemm_choice.py pins the choice
+
+
+def test_sectioned_positions_on_either_prefill_kernel():
+    """The talker's QKV product runs persistent on 64 CUs, which takes the three components apart in a form of its
+    own, and in small tiles on 128: equal bits."""
+    torch = require_gpu()
+    from paper_2608_01785_amd import binding
+    from paper_2608_01785_amd.device_data import DeviceCache, to_device, upload_weights
+    shape = dataclasses.replace(W.TALKER, mrope_sections=SECTIONS[64])
+    lengths, n_img = [PERSISTENT_ROWS - 300, 300], [500, 40]
+    layers = W.make_weights(shape, 1, 121, qkv_bias_std=0.1)
+    batch = W.random_batch(shape.hidden, lengths, seed=122)
+    pos3 = W.mrope_positions(lengths, n_img, grid_w=16)
+    expect, kv = ref.stack_forward(f64(batch.x), weights_f64(layers), shape, batch.seq_offsets, [0, 0], positions3=pos3)
+    offsets = [int(o) for o in batch.seq_offsets]
+    ctx = binding.Context(0, budgets=(64, 128))
+    try:
+        ws = workspace(torch, shape, offsets[-1], 2, max(lengths))
+        wdev, x = upload_weights(layers), to_device(batch.x)
+        got = []
+        for cus in (64, 128):
+            log(f"[mrope] talker {lengths} on {cus} CUs")
+            cache = DeviceCache(1, 2, 832, shape.n_kv_heads, shape.head_dim, fill=0.0)
+            y = torch.full(x.shape, float("nan"), dtype=torch.float32, device="cuda")
+            torch.cuda.synchronize()
+            binding.hs_shared_stage_forward_mrope(ctx, shape, wdev, x, y, offsets, pos3, [0, 0], cache.as_arg(), cus,
+                                                  None, ws)
+            torch.cuda.synchronize()
+            got.append((y.cpu().numpy(), cache.k[0].cpu().numpy(), cache.v[0].cpu().numpy()))
+            k_rows = np.concatenate([h64(cache.rows(0, b, 0, n)[0]) for b, n in enumerate(lengths)])
+            e, ek = err_ratio(got[-1][0], expect), err_ratio(k_rows, kv[0][0])
+            log(f"  max err / rms = {e:.3e} (output), {ek:.3e} (keys)")
+            assert e <= TOL and ek <= TOL
+        for a, b in zip(*got):
+            np.testing.assert_array_equal(a, b)
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
+
+
 def test_talker_decode_step_with_mrope_positions(env):
     torch, ctx = env
     from paper_2608_01785_amd import binding
