@@ -9,7 +9,7 @@ namespace hs {
 
 // Keys per tile (a wave's step: 32 keys, 8 or 16 KB of keys and values) and
 // per split (one block; its four waves take every fourth tile), by head size.
-constexpr int dec_tile_keys(int dh) { return dh == 64 ? 32 : 32; }
+constexpr int kDecTileKeys = 32;
 constexpr int dec_split_keys(int dh) { return dh == 64 ? 1024 : 512; }
 constexpr int dec_splits(int n_keys, int dh) { return (n_keys + dec_split_keys(dh) - 1) / dec_split_keys(dh); }
 

@@ -4,7 +4,7 @@
 // the cache) of one row r and
 // one key/value head g; the group's G query heads are columns of one 16-wide
 // MFMA (G <= 8 valid), so the keys and values of the head are read once for
-// the whole group.  The range is cut into tiles (dec_tile_keys keys); wave w
+// the whole group.  The range is cut into tiles (kDecTileKeys keys); wave w
 // takes tiles w, w + 4, w + 8, ... and keeps its own running softmax state
 // over them.  A tile is loaded as whole lines into registers one tile ahead
 // and passes through a private LDS image of the wave (no barrier; keys, then
@@ -34,7 +34,7 @@ constexpr int kUnitThreads = 256;  // threads per block running a unit
 
 template <int DH>
 struct DecodeSmem {
-  static constexpr int kTile = dec_tile_keys(DH) * DH * 2;  // bytes of a tile's keys, and of its values
+  static constexpr int kTile = kDecTileKeys * DH * 2;  // bytes of a tile's keys, and of its values
   union {
     uint8_t tile[4][kTile];  // [wave] a tile's keys, then its values
     struct {
@@ -64,7 +64,7 @@ __device__ __forceinline__ float quarter_sum(float v) {
 // block of 256 threads.
 template <int DH>
 __device__ __forceinline__ void decode_attn_unit(const DecodeAttnArgs& a, int item, int g, DecodeSmem<DH>& sm) {
-  constexpr int TK = dec_tile_keys(DH);        // keys per tile
+  constexpr int TK = kDecTileKeys;        // keys per tile
   constexpr int NKB = DH / 32;                 // 32-wide K steps of q.k
   constexpr int NDS = DH / 16;                 // output subtiles along dh
   constexpr int kTile = DecodeSmem<DH>::kTile;

@@ -76,15 +76,6 @@ __device__ __forceinline__ uint32_t weight_row(int tile_n, int r, int ffn) {
 // touches each of the 64 banks once (and any 8 consecutive rows each of 32).
 __device__ __forceinline__ int swz(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
 
-// silu(z) = z / (1 + e^-z), with the hardware reciprocal (1 ulp) in place of
-// an IEEE division: the result is rounded to fp16 next.
-__device__ __forceinline__ float silu(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
-
-// Buffer resource over [base, base + bytes): loads past the end return zero.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
-}
-
 template <int EPI, int DH, bool W_F16>
 __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs a) {
   __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * kStageBytes];
@@ -422,18 +413,15 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs a) {
                                __uint_as_float(cur.b.y << 16), __uint_as_float(cur.b.y & 0xffff0000u)};
           f32x4 v;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = cur.r[e] + cur.gt[e] * (acc[i][j][4 * g + e] + b4[e]);
+          for (int e = 0; e < 4; ++e) v[e] = gated(cur.r[e], cur.gt[e], acc[i][j][4 * g + e], b4[e]);
           *reinterpret_cast<f32x4*>(orow + i * 32 + 8 * g) = v;
         }
       } else if constexpr (EPI == EPI_GELU) {
-        // out (fp16) = gelu_tanh(products + bias); 0.5 z (1 + tanh(u)) = z / (1 + exp(-2u))
-        // with u = sqrt(2 / pi) (z + 0.044715 z^3), and exp(-2u) = 2^(z (k1 + k2 z^2)),
-        // k1 = -2 sqrt(2 / pi) log2(e), k2 = 0.044715 k1.  Groups 2p and 2p + 1
+        // out (fp16) = gelu_tanh(products + bias).  Groups 2p and 2p + 1
         // are stored as one 32-byte run of the row, and each pair's bias is
         // loaded before the previous pair's store: stores count against the
         // same completion counter as loads, so waiting for it never waits for
         // a store.
-        constexpr float k1 = -2.302208198144325f, k2 = -0.1029432395800235f;
         const int n_base = tile_n * BN + wn * 128;
         uint16_t* orow = a.out + int64_t(m) * a.ldo + n_base;
         const uint16_t* brow = a.bias + n_base + 4 * fh;
@@ -455,10 +443,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm_kernel(GemmArgs a) {
             const float b4[4] = {__uint_as_float(b[h].x << 16), __uint_as_float(b[h].x & 0xffff0000u),
                                  __uint_as_float(b[h].y << 16), __uint_as_float(b[h].y & 0xffff0000u)};
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float z = acc[i][j][8 * p + 4 * h + e] + b4[e];
-              v[h][e] = z * __builtin_amdgcn_rcpf(1.0f + exp2_raw(z * fmaf(z * z, k2, k1)));
-            }
+            for (int e = 0; e < 4; ++e) v[h][e] = gelu(acc[i][j][8 * p + 4 * h + e] + b4[e]);
           }
           store_h8_pair(orow + i * 32 + 16 * p, fh, v[0], v[1]);
         }

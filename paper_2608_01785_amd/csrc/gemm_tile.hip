@@ -50,12 +50,6 @@ __device__ __forceinline__ uint32_t strip_row(int strip, int r, int ffn) {
 // different halves.
 __device__ __forceinline__ int phys(int r, int c) { return c ^ ((r >> 1) & 7) ^ ((r & 1) << 2); }
 
-__device__ __forceinline__ float silu(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
-}
-
 // One row subtile's outputs: accumulator c of strip `strip`, activation row m.
 template <int EPI, int DH>
 __device__ __forceinline__ void store_rows(const GemmArgs& a, const f32x16& c, int strip, int m, int fh) {
@@ -87,11 +81,10 @@ __device__ __forceinline__ void store_rows(const GemmArgs& a, const f32x16& c, i
     for (int g = 0; g < 4; ++g) {
       f32x4 v;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = r[g][e] + gt[g][e] * (c[4 * g + e] + b[g][e]);
+      for (int e = 0; e < 4; ++e) v[e] = gated(r[g][e], gt[g][e], c[4 * g + e], b[g][e]);
       *reinterpret_cast<f32x4*>(orow + 8 * g) = v;
     }
   } else if constexpr (EPI == EPI_GELU) {
-    constexpr float k1 = -2.302208198144325f, k2 = -0.1029432395800235f;  // see gemm.hip
     uint16_t* orow = a.out + int64_t(m) * a.ldo + strip * 32;
     const uint16_t* brow = a.bias + strip * 32 + 4 * fh;
 #pragma unroll
@@ -102,10 +95,7 @@ __device__ __forceinline__ void store_rows(const GemmArgs& a, const f32x16& c, i
         float b[4];
         load_bf16x4(brow + 16 * p + 8 * h, b);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float z = c[8 * p + 4 * h + e] + b[e];
-          v[h][e] = z * __builtin_amdgcn_rcpf(1.0f + exp2_raw(z * fmaf(z * z, k2, k1)));
-        }
+        for (int e = 0; e < 4; ++e) v[h][e] = gelu(c[8 * p + 4 * h + e] + b[e]);
       }
       store_h8_pair(orow + 16 * p, fh, v[0], v[1]);
     }

@@ -290,6 +290,32 @@ __device__ __forceinline__ int rope_pos(const Args& a, int m, int j) {
   return a.pos[c * a.pos_stride + m];
 }
 
+// Buffer resource over [base, base + bytes): loads past the end return zero.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+}
+
+// Epilogue arithmetic, one definition for all GEMMs: which of them runs must
+// change no bit, so the roundings are spelled out where a compiler could
+// choose.
+
+// silu(z) = z / (1 + e^-z), with the hardware reciprocal (1 ulp) in place of
+// an IEEE division: the result is rounded to fp16 next.
+__device__ __forceinline__ float silu(float z) { return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
+
+// gelu_tanh(z) = 0.5 z (1 + tanh(u)) = z / (1 + exp(-2u)) with
+// u = sqrt(2 / pi) (z + 0.044715 z^3), and exp(-2u) = 2^(z (k1 + k2 z^2)),
+// k1 = -2 sqrt(2 / pi) log2(e), k2 = 0.044715 k1.
+__device__ __forceinline__ float gelu(float z) {
+  constexpr float k1 = -2.302208198144325f, k2 = -0.1029432395800235f;
+  return z * __builtin_amdgcn_rcpf(1.0f + exp2_raw(z * fmaf(z * z, k2, k1)));
+}
+
+// resid + gate (product + bias), the adaLN-Zero residual branch.
+__device__ __forceinline__ float gated(float resid, float gate, float product, float bias) {
+  return fmaf(gate, product + bias, resid);
+}
+
 // One rotation pair of the prefill GEMMs: (lo, hi) -> (lo cos - hi sin,
 // hi cos + lo sin), with the roundings spelled out so that the persistent
 // kernel and every tile shape give the same bits.  (The skinny GEMM's
