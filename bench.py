@@ -34,23 +34,24 @@ SPEC_MHZ = 2400.0        # clock of the published peak
 # HBM-side bytes per gate/up launch at 256 CUs from rocprofv3 FETCH_SIZE and
 # WRITE_SIZE passes (KiB per dispatch), each scaled by what the counter reads for a
 # 1 GiB device copy (fetch x 2.000, write x 1.000).  Valid only for the GEMM
-# source these counters were taken on.
+# sources these counters were taken on.
 MEASURED_TRAFFIC = {
-    "35c5cac0be380a8f": {"fetch_kib": 2241038.6, "fetch_scale": 2.0, "write_kib": 397954.7, "write_scale": 1.0},
-    "b13966ab4f6ab1ce": {"fetch_kib": 2240940.5, "fetch_scale": 2.0, "write_kib": 400059.4, "write_scale": 1.0},
-    "03c73fb21179ef2c": {"fetch_kib": 2241088.2, "fetch_scale": 2.0, "write_kib": 399894.8, "write_scale": 1.0},
-    "f9d19f9ce46f207e": {"fetch_kib": 2245197.3, "fetch_scale": 2.0, "write_kib": 399491.4, "write_scale": 1.0},
-    "e964d3aa53b0007d": {"fetch_kib": 2224511.9, "fetch_scale": 2.0, "write_kib": 397264.2, "write_scale": 1.0},
-    "d4915bf77392150d": {"fetch_kib": 2226951.2, "fetch_scale": 2.0, "write_kib": 397023.8, "write_scale": 1.0},
-    "adc65d4733f8721b": {"fetch_kib": 2315757.9, "fetch_scale": 2.0, "write_kib": 395098.1, "write_scale": 1.0},
+    "66e030ceec851878": {"fetch_kib": 2315422.8, "fetch_scale": 2.0, "write_kib": 395184.3, "write_scale": 1.0},
 }
 
 
-def gemm_traffic_bytes():
+def gemm_source_key():
+    """Hash of everything a prefill GEMM launch is compiled from and chosen by."""
     import hashlib
-    with open(os.path.join(ROOT, "paper_2608_01785_amd", "csrc", "gemm.hip"), "rb") as f:
-        key = hashlib.sha256(f.read()).hexdigest()[:16]
-    m = MEASURED_TRAFFIC.get(key)
+    h = hashlib.sha256()
+    for name in ("gemm.hip", "gemm_tile.hip", "gemm_policy.h", "hs_device.h", "hs_kernels.h"):
+        with open(os.path.join(ROOT, "paper_2608_01785_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
+
+
+def gemm_traffic_bytes():
+    m = MEASURED_TRAFFIC.get(gemm_source_key())
     if m is None:
         return None
     return int(1024 * (m["fetch_kib"] * m["fetch_scale"] + m["write_kib"] * m["write_scale"]))

@@ -1,8 +1,8 @@
 // Diffusion-transformer pieces for gfx950: the adaLN modulation of each
 // sequence and the modulated LayerNorm that feeds a block's QKV and MLP
-// GEMMs.  The projections themselves run on the persistent GEMM (gemm.hip)
-// with its bias + gated-residual and bias + GELU epilogues, and attention on
-// the prefill kernel in its bidirectional mode.
+// GEMMs.  The projections themselves run on the prefill GEMMs (gemm.hip,
+// gemm_tile.hip) with their bias + gated-residual and bias + GELU epilogues,
+// and attention on the prefill kernel in its bidirectional mode.
 #include "hs_device.h"
 #include "hs_kernels.h"
 

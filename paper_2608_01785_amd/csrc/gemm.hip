@@ -34,6 +34,9 @@
 // the loads of a tile's last four stages already fetch the next tile's first
 // four: the pipeline runs across tiles and the epilogue overlaps them.
 //
+// Shapes with too few such tiles for the budget's CUs run in smaller ones
+// (gemm_tile.hip; gemm_policy.h chooses), with the same bits.
+//
 // The grid is persistent (one block per CU of the budget); blocks walk the
 // tile space in grouped order, remapped so each XCD takes a contiguous range,
 // and in alternating block order from round to round.

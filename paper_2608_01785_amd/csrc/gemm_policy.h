@@ -33,13 +33,16 @@ constexpr float kGemmTileMargin = 0.93f;
 // the choice may follow the budget.  It is a matter of rounds: a CU's time is
 // the tiles it gets times the time of a tile, and a 256 x 256 tile (cheapest
 // per product, 1.35 us a stage against 4 x 0.46) only pays when there are
-// several per CU.  The constants are a least-squares fit to 230 timed
-// launches (M 130 .. 10515, the four layer shapes' N and K, 64 .. 256 CUs):
-// the choice is within 1.6 % of the fastest shape on average and was never
-// more than 2 % behind the persistent kernel; over the sweep it takes half
-// the persistent kernel's time.  At 389 x 3584 x 18944 on 160 CUs: 332 us
-// persistent, 114 us in 128 x 96 tiles; at 9151 x 3584 x 18944 on 256 CUs 1094
-// against 1174 (256 x 192), so large batches keep the persistent kernel.
+// several per CU.  The constants were fitted to launches with fp16 weights;
+// epilogue and weight format do not enter.  tests/gemm_rule_sweep.py times
+// all eight kernels over eleven products with their own epilogues, 130 to 9151
+// rows and six budgets: the choice takes 0.8 % more than the fastest kernel on
+// average with fp16 weights and 3.2 % with bf16 ones (19 and 30 % at most, one
+// row count before the next shape pays), at most 2.5 % more than the
+// persistent kernel (6500 x 3584 x 18944 on 96 CUs), and half its time in the
+// geometric mean.  At 389 x 3584 x 18944 on 160 CUs: 336 us persistent, 116 in
+// 128 x 96 tiles; at 9151 x 3584 x 18944 on 256 CUs 1080 against 1181
+// (256 x 192), so large batches keep the persistent kernel.
 inline int gemm_tile_choice(int M, int N, int K, int cus) {
   const float stages = float(K) / 64.0f;
   auto up = [](int64_t a, int64_t b) { return int64_t((a + b - 1) / b); };

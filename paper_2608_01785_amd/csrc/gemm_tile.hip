@@ -3,7 +3,8 @@
 //
 // Same contraction and epilogues as the persistent GEMM (gemm.hip), and the
 // same accumulation order per output element (K ascending in 16-wide MFMA
-// steps, residual first), so which of the two runs changes no bit.
+// steps, residual first), so which of the two runs changes no bit
+// (tests/test_gpu_gemm_kernels.py).
 //
 // A block is WN x WM waves over a tile of 32 NS WN weight rows x 32 MT WM
 // activation rows; K advances in stages of 64 through two LDS buffers, fetched

@@ -255,7 +255,8 @@ uint64_t* clock_slot(const hs_context* ctx) {
     timing_end(ctx, s, kind, ta_, tb_);                \
   } while (0)
 
-// Large persistent GEMM, or the skinny variant for decode-sized batches.
+// Prefill GEMM (persistent or in small tiles, see launch_gemm), or the skinny
+// variant for decode-sized batches.
 hipError_t gemm(int epi, const hs::GemmArgs& a, int grid_cap, hipStream_t s) {
   if (hs::skinny_supported(epi, a)) return hs::launch_gemm_skinny(epi, a, s);
   return hs::launch_gemm(epi, a, grid_cap, s);
@@ -332,7 +333,7 @@ hs_status launch_layers(hs_context* ctx, const LaunchSet& L, hipStream_t s) {
   // SwiGLU output) k-group-major, the skinny GEMM's operand layout.
   const int k8 = T <= hs::kSkinnyMaxRows ? hs::skinny_k8_rows(T) : 0;
 
-  const int grid_cap = budget;  // persistent GEMM: one block per CU of the budget
+  const int grid_cap = budget;  // CUs of the budget: the persistent GEMM's blocks, and what chooses its kernel
   const float scale_log2 = 1.4426950408889634f / sqrtf(float(dh));
   // The residual stream is bf16 only at the input; every layer writes fp32.
   const uint16_t* x_cur = static_cast<const uint16_t*>(L.x_in);

@@ -11,9 +11,15 @@
 // RoPE + key/value store).  A K split publishes fp32 partial sums; the last
 // split of a strip to arrive adds them in split order.
 //
-// What bounds it is memory, once the loads are whole lines: fragments fetched
-// straight from memory put adjacent lanes in different weight rows, which
-// costs a CU's address unit about 93 cycles per 1 KB against 17.
+// What bounds it, for large weights and up to 32 rows, is memory, once the
+// loads are whole lines: fragments fetched straight from memory put adjacent
+// lanes in different weight rows, which costs a CU's address unit about 93
+// cycles per 1 KB against 17 (gate/up of a 3584-wide layer, 272 MB on 256 CUs:
+// 55 us, 4.9 TB/s).  Small weights take a launch's latencies: 7 to 9 us for 2
+// to 17 MB on 128 CUs.  With 65 to 128 rows (MT = 4) it is neither: every strip
+// reads the same activations again, 16 KB a stage beside 4 or 8 KB of weights,
+// and registers and LDS leave one block a CU: 10 to 15 us for the same weights
+// on 160 CUs.
 //
 // Weights are bf16 row-major or prepared fp16 panel-major ([K / 32][N][32]).
 // The weight strip is the MFMA A operand and activation rows the B operand, so

@@ -17,8 +17,9 @@ def choice(M, N, K, cus):
     return binding.lib().hs_gemm_choice(M, N, K, cus)
 
 
-def run(epi, kernel, cus=256, **args):
-    """Tensors and numbers by field name; missing ones are zero.  Runs on the default stream."""
+def call(epi, kernel, cus=256, stream=None, **args):
+    """A launch, ready to be made: tensors and numbers by field name, missing ones zero.  stream: a handle, or the
+    default stream."""
     unknown = set(args) - set(FIELDS)
     assert not unknown, unknown
     vals = [args.get(f, 0) for f in FIELDS]
@@ -27,7 +28,15 @@ def run(epi, kernel, cus=256, **args):
     arr = (ctypes.c_int64 * len(FIELDS))(*[t if isinstance(t, int) else t.data_ptr() for t in vals])
     fn = binding.lib().hs_gemm_direct
     fn.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p]
-    binding._check(fn(epi, kernel, cus, arr, len(FIELDS), None))
+
+    def launch():
+        binding._check(fn(epi, kernel, cus, arr, len(FIELDS), stream))
+    launch.tensors = vals   # alive as long as the call
+    return launch
+
+
+def run(epi, kernel, cus=256, **args):
+    call(epi, kernel, cus, **args)()
 
 
 def panels(w):
