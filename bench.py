@@ -61,6 +61,29 @@ def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
 
+# Sections of the result that go to the log in full and not into the result line.
+DETAILS = ("mixed_corun", "decode_tpot_vs_cus", "policy_model", "serving_loop")
+
+
+def finite(v):
+    """v with every non-finite number as null: NaN and infinities are not JSON."""
+    if isinstance(v, dict):
+        return {k: finite(x) for k, x in v.items()}
+    if isinstance(v, (list, tuple)):
+        return [finite(x) for x in v]
+    return None if isinstance(v, float) and not np.isfinite(v) else v
+
+
+def result_line(out):
+    """(the result line, the details): strict JSON both, the line a few KB whatever was measured."""
+    out = finite(out)
+    details = {k: out[k] for k in DETAILS if out.get(k) is not None}
+    line = {k: v for k, v in out.items() if k not in DETAILS}
+    if details.get("serving_loop"):
+        line["serving_loop"] = {"mean_over_seeds": details["serving_loop"].get("mean_over_seeds")}
+    return json.dumps(line, allow_nan=False), json.dumps(details, allow_nan=False)
+
+
 def thinker_flops(shape, lengths, ctx=None):
     """Algorithmic FLOPs of one layer: 2 * params per row + 4 * Hq * dh per visible (query, key) pair."""
     L = np.asarray(lengths, np.int64)
@@ -348,7 +371,9 @@ def main():
         "serving_loop": loop,
         "cpu_baseline": cpu,
     }
-    print(json.dumps(out), flush=True)
+    line, details = result_line(out)
+    log("[bench] details " + details)
+    print(line, flush=True)
     torch.cuda.synchronize()
     ctx.close()
 
