@@ -15,7 +15,8 @@ namespace {
 enum Field {
   kA, kW, kWF16, kM, kK, kN, kOut, kOutF32, kLdo, kResid, kResidF32, kFfn, kQ, kKeys, kValues, kPos, kPosStride,
   kSec1, kSec2, kKOff, kVOff, kKvHeadStride, kRope, kBias, kGate, kGateStride, kRowSeq, kHq, kHkv, kDh, kPart,
-  kCounters, kK8Rows, kClock, kFields
+  kCounters, kK8Rows, kClock,
+  kWResident, kFields
 };
 
 constexpr int kSkinnyKernel = -2, kPersistentKernel = -1;  // tile shapes count from 0
@@ -67,6 +68,7 @@ hs_status hs_gemm_direct(int32_t epi, int32_t kernel, int32_t cus, const int64_t
   a.counters = i32(kCounters);
   a.k8_rows = int(v[kK8Rows]);
   a.clock = reinterpret_cast<uint64_t*>(v[kClock]);
+  a.w_resident = int(v[kWResident]);
 
   const bool skinny = kernel == kSkinnyKernel;
   const int64_t limit = int64_t(1) << 32;

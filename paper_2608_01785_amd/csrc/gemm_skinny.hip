@@ -8,19 +8,22 @@ namespace {
 using namespace skinny;
 
 // NS: n-subtiles of 32 weight rows per block (1 or 2); MT: m-subtiles of 32
-// rows.
-template <int EPI, int DH, bool W_F16, int NS, int MT>
+// rows; FRAG: weights as fragments instead of whole lines
+// (skinny_frag_stages() says when).
+template <int EPI, int DH, bool W_F16, int NS, int MT, bool FRAG>
 __global__ __launch_bounds__(kThreads) void skinny_kernel(GemmArgs a) {
   __shared__ __attribute__((aligned(1024))) uint8_t smem[SkinnyShape<NS, MT>::SMEM];
-  skinny_unit<EPI, DH, W_F16, NS, MT>(a, blockIdx.x / a.n_split, blockIdx.x % a.n_split, smem);
+  skinny_unit<EPI, DH, W_F16, NS, MT, FRAG>(a, blockIdx.x / a.n_split, blockIdx.x % a.n_split, smem);
 }
 
 template <int EPI, int DH, int NS, int MT>
 hipError_t launch_mt(const GemmArgs& a, int n_blocks, hipStream_t s) {
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(n_blocks), dim3(kThreads), 0, s, a); };
+  const bool frag = a.k_per_split <= skinny_frag_stages(NS, MT, a.w_f16, a.w_resident);
   if (a.w_f16)
-    hipLaunchKernelGGL((skinny_kernel<EPI, DH, true, NS, MT>), dim3(n_blocks), dim3(kThreads), 0, s, a);
+    frag ? launch(skinny_kernel<EPI, DH, true, NS, MT, true>) : launch(skinny_kernel<EPI, DH, true, NS, MT, false>);
   else
-    hipLaunchKernelGGL((skinny_kernel<EPI, DH, false, NS, MT>), dim3(n_blocks), dim3(kThreads), 0, s, a);
+    frag ? launch(skinny_kernel<EPI, DH, false, NS, MT, true>) : launch(skinny_kernel<EPI, DH, false, NS, MT, false>);
   return hipGetLastError();
 }
 

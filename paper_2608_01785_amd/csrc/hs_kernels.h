@@ -66,6 +66,9 @@ struct GemmArgs {
   // Skinny GEMM only: A, out and scaled_out are k-group-major with this many
   // padded rows (skinny_k8_rows(M)); 0 = row-major.
   int k8_rows;
+  // Skinny GEMM: the weights of all the call's layers fit the last-level cache
+  // (kSkinnyResidentBytes).
+  int w_resident;
   // Timing mode: four counters of the launch, zero on entry (see LaunchClock
   // and TileClock), or null.
   uint64_t* clock;

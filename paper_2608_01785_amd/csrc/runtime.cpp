@@ -334,6 +334,8 @@ hs_status launch_layers(hs_context* ctx, const LaunchSet& L, hipStream_t s) {
   const int k8 = T <= hs::kSkinnyMaxRows ? hs::skinny_k8_rows(T) : 0;
 
   const int grid_cap = budget;  // CUs of the budget: the persistent GEMM's blocks, and what chooses its kernel
+  const int64_t layer_bytes = 2 * (int64_t(hq + 2 * hkv) * dh * d + int64_t(hq) * dh * d + 3 * int64_t(f) * d);
+  const int w_resident = n_layers * layer_bytes <= hs::kSkinnyResidentBytes;
   const float scale_log2 = 1.4426950408889634f / sqrtf(float(dh));
   // The residual stream is bf16 only at the input; every layer writes fp32.
   const uint16_t* x_cur = static_cast<const uint16_t*>(L.x_in);
@@ -375,6 +377,7 @@ hs_status launch_layers(hs_context* ctx, const LaunchSet& L, hipStream_t s) {
     g.hkv = hkv;
     g.dh = dh;
     g.k8_rows = k8;
+    g.w_resident = w_resident;
     if (folded) use_norm(g, sumsq, norm_parts, cfg->rms_eps);
     g.clock = clock_slot(ctx);
     TIMED(HS_KERNEL_QKV, gemm(hs::EPI_QKV, g, grid_cap, s));
@@ -435,6 +438,7 @@ hs_status launch_layers(hs_context* ctx, const LaunchSet& L, hipStream_t s) {
     go.resid = x_cur;
     go.resid_f32 = x_cur_f32;
     go.k8_rows = k8;
+    go.w_resident = w_resident;
     // Fold when every GEMM of the layer takes the skinny path (gate/up and
     // down share M, and their K are multiples of 64) and a consumer can
     // prefetch a row's partial sums.
@@ -460,6 +464,7 @@ hs_status launch_layers(hs_context* ctx, const LaunchSet& L, hipStream_t s) {
     gu.ldo = f;
     gu.ffn = f;
     gu.k8_rows = k8;
+    gu.w_resident = w_resident;
     if (fold) use_norm(gu, sumsq, norm_parts, cfg->rms_eps);
     gu.clock = clock_slot(ctx);
     TIMED(HS_KERNEL_GATE_UP, gemm(hs::EPI_SWIGLU, gu, grid_cap, s));
@@ -477,6 +482,7 @@ hs_status launch_layers(hs_context* ctx, const LaunchSet& L, hipStream_t s) {
     gd.ldo = d;
     gd.resid_f32 = h_buf;
     gd.k8_rows = k8;
+    gd.w_resident = w_resident;
     folded = fold && l + 1 < n_layers;
     if (folded) fold_norm(gd, sumsq, n_buf, w[l + 1].ln1);
     gd.clock = clock_slot(ctx);

@@ -3,23 +3,26 @@
 // Decode re-reads every weight for a handful of rows, so the unit streams W
 // rather than reusing it: a block owns a thin strip of weight rows (32, or 64
 // when the epilogue needs RoPE or gate/up pairs), all M rows and one K range.
-// The four waves split the range into interleaved stages of 64; a wave loads a
-// stage's weights as whole lines into registers, two stages ahead, and passes
-// them through an LDS image of its own into MFMA layout, so no wave waits on
-// another until the end, where partial accumulators are summed through LDS
-// and the fused epilogues run (residual add into fp32, SwiGLU, or
-// RoPE + key/value store).  A K split publishes fp32 partial sums; the last
-// split of a strip to arrive adds them in split order.
+// The four waves split the range among them and load their weights and
+// activations into registers two steps ahead, so no wave waits on another
+// until the end, where partial accumulators are summed through LDS and the
+// fused epilogues run (residual add into fp32, SwiGLU, or RoPE + key/value
+// store).  A K split publishes fp32 partial sums; the last split of a strip to
+// arrive adds them in split order.
+//
+// The weights come in one of two ways (FRAG).  A short K: as fragments in MFMA
+// layout, straight from memory, in chunks of one or two 32-wide panels.  A
+// long K: stages of 64 as whole lines, through an LDS image of the wave's own
+// into MFMA layout.  skinny_frag_stages() draws the line.
 //
 // What bounds it, for large weights and up to 32 rows, is memory, once the
-// loads are whole lines: fragments fetched straight from memory put adjacent
-// lanes in different weight rows, which costs a CU's address unit about 93
-// cycles per 1 KB against 17 (gate/up of a 3584-wide layer, 272 MB on 256 CUs:
-// 55 us, 4.9 TB/s).  Small weights take a launch's latencies: 7 to 9 us for 2
-// to 17 MB on 128 CUs.  With 65 to 128 rows (MT = 4) it is neither: every strip
-// reads the same activations again, 16 KB a stage beside 4 or 8 KB of weights,
-// and registers and LDS leave one block a CU: 10 to 15 us for the same weights
-// on 160 CUs.
+// loads are whole lines: fragments put adjacent lanes in different weight
+// rows, which costs a CU's address unit about 93 cycles per 1 KB against 17
+// (gate/up of a 3584-wide layer, 272 MB on 256 CUs: 55 us, 4.9 TB/s).  Small
+// weights take a launch's latencies: 7 to 9 us for 2 to 17 MB on 128 CUs.  With
+// 65 to 128 rows (MT = 4) it is neither: every strip reads the same activations
+// again, 16 KB a stage beside 4 or 8 KB of weights, and registers and LDS leave
+// one block a CU: 10 to 15 us for the same weights.
 //
 // Weights are bf16 row-major or prepared fp16 panel-major ([K / 32][N][32]).
 // The weight strip is the MFMA A operand and activation rows the B operand, so
@@ -74,7 +77,7 @@ constexpr int kSets = 2;  // stages in flight per wave, and walked per iteration
 // One weight strip (`tile`) and one K split (`ks`) of a skinny GEMM, by one
 // block of kThreads threads, in LDS `smem` (SkinnyShape::SMEM bytes, 1 KB
 // aligned).
-template <int EPI, int DH, bool W_F16, int NS, int MT>
+template <int EPI, int DH, bool W_F16, int NS, int MT, bool FRAG>
 __device__ __forceinline__ void skinny_unit(const GemmArgs& a, int tile, int ks, uint8_t* smem) {
   constexpr int NR = 32 * NS;                 // weight rows per block
   constexpr int S = kSets;
@@ -147,11 +150,11 @@ __device__ __forceinline__ void skinny_unit(const GemmArgs& a, int tile, int ks,
   const __amdgpu_buffer_rsrc_t xres =
       make_rsrc(a.A, a.k8_rows ? uint32_t(a.K) * uint32_t(a.k8_rows) * 2 : uint32_t(a.M) * row_bytes);
 
-  // Wave w takes stages w, w + 4, w + 8, ... of the split, in pairs, S of them
-  // in flight.  A stage past the range (the second of an odd last pair, both
-  // of a wave without stages) is read through an empty buffer resource: zeros,
-  // no traffic, products that add nothing, and the same loads in every
-  // iteration, so the wait counts stay exact.
+  // Whole lines: wave w takes stages w, w + 4, w + 8, ... of the split, in
+  // pairs, S of them in flight.  A stage past the range is read through an
+  // empty buffer resource (zeros, no traffic), so every iteration issues the
+  // same loads and the wait counts stay exact; the second of an odd last pair
+  // is not multiplied.
   //   weight fragment (A operand): rows strip_row(i * 32 + fr), K 16 s + 8 fh .. + 7
   //   activation fragment (B operand): rows j * 32 + fr, the same K
   // Every weight load of a wave covers 1 KB in runs of 64 bytes or more: 16
@@ -228,8 +231,8 @@ __device__ __forceinline__ void skinny_unit(const GemmArgs& a, int tile, int ks,
   // stage i's products hides the LDS latency, but then the activations of
   // stage i + 2 are not asked for before the weights of stage i + 1 are
   // there: three latencies, and loads past the end besides (talker step of
-  // one row, two layers, 64 CUs: 83.3 us, now 76.7; 16 layers of 32 rows on
-  // 128 CUs 880, now 850; one thinker layer of 4 rows 195, now 192).
+  // one row, two layers, 64 CUs: 83.3 us against 76.7; 16 layers of 32 rows on
+  // 128 CUs 880 against 850; one thinker layer of 4 rows 195 against 192).
   // The lanes read each other's chunks: LDS accesses of a wave complete in
   // order, so keeping the program order is enough.
   auto stage = [&](int i, Stage& b, auto next) {
@@ -259,12 +262,66 @@ __device__ __forceinline__ void skinny_unit(const GemmArgs& a, int tile, int ks,
     if constexpr (decltype(next)::value) load_x(i + S, b);
   };
 
-  Stage st[S];
-  __builtin_amdgcn_sched_barrier(0);
+  // FRAG: the wave's 32-wide panels w, w + 4, w + 8, ... of the split, as
+  // fragments, in chunks of CH panels: chunk c + 1 is loaded while chunk c is
+  // multiplied, chunk 0 always (a panel past the range reads zeros), later
+  // ones only when they hold panels, so the wait counts stay exact.
+  constexpr int CH = NS + MT <= 3 ? 2 : 1;
+  const int n_panels = 2 * KT;
+  const int my_panels = n_panels > wave ? (n_panels - wave + 3) / 4 : 0;
+  const int n_chunks = (my_panels + CH - 1) / CH;
+  struct Chunk {
+    u32x4 w[CH][2][NS];
+    u32x4 x[CH][2][MT];
+  };
+  uint32_t f_off[NS];
 #pragma unroll
-  for (int u = 0; u < S; ++u) {
-    load_w(u, st[u]);
-    load_x(u, st[u]);
+  for (int n = 0; n < NS; ++n)
+    f_off[n] = strip_row<EPI, NR, DH>(tile, n * 32 + fr, a.ffn) * (W_F16 ? 64u : row_bytes) + uint32_t(fh * 16);
+  auto load_chunk = [&](int c, Chunk& b) {
+#pragma unroll
+    for (int q = 0; q < CH; ++q) {
+      const int p = wave + 4 * (c * CH + q);  // panel of this split
+      const __amdgpu_buffer_rsrc_t wr = p < n_panels ? wres : zres;
+      const __amdgpu_buffer_rsrc_t xr = p < n_panels ? xres : zres;
+      const uint32_t P = uint32_t(2 * kt0 + p);  // panel of the matrix
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+#pragma unroll
+        for (int n = 0; n < NS; ++n)
+          b.w[q][s][n] = __builtin_amdgcn_raw_buffer_load_b128(wr, f_off[n] + 32 * s, P * (W_F16 ? panel_bytes : 64u), 0);
+#pragma unroll
+        for (int j = 0; j < MT; ++j)
+          b.x[q][s][j] = __builtin_amdgcn_raw_buffer_load_b128(xr, x_off[j] + x_step * s, P * 2 * x_step, 0);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto mma_chunk = [&](const Chunk& b) {
+#pragma unroll
+    for (int q = 0; q < CH; ++q)
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int n = 0; n < NS; ++n) {
+          const u32x4 wh = W_F16 ? b.w[q][s][n] : bf8_to_h8(b.w[q][s][n]);
+#pragma unroll
+          for (int j = 0; j < MT; ++j) acc[n][j] = mfma32(wh, b.x[q][s][j], acc[n][j]);
+        }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  Stage st[S];
+  Chunk b0, b1;
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (FRAG) {
+    load_chunk(0, b0);
+  } else {
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+      load_w(u, st[u]);
+      load_x(u, st[u]);
+    }
   }
   // QKV: the RoPE table entries of this lane's dimension pairs and, with a
   // bias, the bias of its columns (registers 4 g + e: dimension
@@ -294,15 +351,32 @@ __device__ __forceinline__ void skinny_unit(const GemmArgs& a, int tile, int ks,
     }
     __builtin_amdgcn_sched_barrier(0);
   }
-  constexpr std::true_type more{};
-  constexpr std::false_type done{};
-  int i = 0;
-  for (; i + S < my_stages; i += S) {
-    stage(i, st[0], more);
-    stage(i + 1, st[1], more);
+  if constexpr (FRAG) {
+    int c = 0;
+    for (; c + 2 < n_chunks; c += 2) {
+      load_chunk(c + 1, b1);
+      mma_chunk(b0);
+      load_chunk(c + 2, b0);
+      mma_chunk(b1);
+    }
+    if (n_chunks - c == 2) {
+      load_chunk(c + 1, b1);
+      mma_chunk(b0);
+      mma_chunk(b1);
+    } else if (n_chunks - c == 1) {
+      mma_chunk(b0);
+    }
+  } else {
+    constexpr std::true_type more{};
+    constexpr std::false_type done{};
+    int i = 0;
+    for (; i + S < my_stages; i += S) {
+      stage(i, st[0], more);
+      stage(i + 1, st[1], more);
+    }
+    stage(i, st[0], done);
+    if (i + 1 < my_stages) stage(i + 1, st[1], done);
   }
-  stage(i, st[0], done);
-  stage(i + 1, st[1], done);
 
   // Sum the four waves' partial accumulators through LDS ([wave][i][j][lane]
   // images of 16 floats, moved 16 bytes at a time); wave w then owns row

@@ -9,7 +9,7 @@ TILES = range(7)
 
 FIELDS = ("A", "W", "w_f16", "M", "K", "N", "out", "out_f32", "ldo", "resid", "resid_f32", "ffn", "q", "k", "v", "pos",
           "pos_stride", "sec1", "sec2", "k_off", "v_off", "kv_head_stride", "rope", "bias", "gate", "gate_stride",
-          "row_seq", "hq", "hkv", "dh", "part", "counters", "k8_rows", "clock")
+          "row_seq", "hq", "hkv", "dh", "part", "counters", "k8_rows", "clock", "w_resident")
 
 
 def choice(M, N, K, cus):
