@@ -37,11 +37,11 @@ constexpr float kGemmTileMargin = 0.93f;
 // epilogue and weight format do not enter.  tests/gemm_rule_sweep.py times
 // all eight kernels over eleven products with their own epilogues, 130 to 9151
 // rows and six budgets: the choice takes 0.8 % more than the fastest kernel on
-// average with fp16 weights and 3.2 % with bf16 ones (19 and 30 % at most, one
-// row count before the next shape pays), at most 2.5 % more than the
-// persistent kernel (6500 x 3584 x 18944 on 96 CUs), and half its time in the
-// geometric mean.  At 389 x 3584 x 18944 on 160 CUs: 336 us persistent, 116 in
-// 128 x 96 tiles; at 9151 x 3584 x 18944 on 256 CUs 1080 against 1181
+// average with fp16 weights and 3.2 % with bf16 ones (20 and 29 % at most, one
+// row count before the next shape pays), at most 2.6 % more than the
+// persistent kernel (9151 x 3584 x 18944 on 96 CUs), and half its time in the
+// geometric mean.  At 389 x 3584 x 18944 on 160 CUs: 337 us persistent, 112 in
+// 128 x 96 tiles; at 9151 x 3584 x 18944 on 256 CUs 1036 against 1124
 // (256 x 192), so large batches keep the persistent kernel.
 inline int gemm_tile_choice(int M, int N, int K, int cus) {
   const float stages = float(K) / 64.0f;
